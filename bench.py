@@ -91,8 +91,8 @@ KERNEL_SOURCES = {
 KERNEL_NAMES = {
     "forward": ["k_forward"],
     # with the backward workspace, as the step runs them
-    "backward": ["k_backward_init", "k_backward_short", "k_backward_list"],
-    "backward_update": ["k_backward_init", "k_backward_short", "k_backward_list"],
+    "backward": ["k_backward_list", "k_backward_rows", "k_backward_short"],
+    "backward_update": ["k_backward_list", "k_backward_rows", "k_backward_short"],
     "update": ["k_sparse_update"],
     "cast": ["k_cast_small", "k_build_keys", "k_radix_hist", "k_radix_scan", "k_radix_scatter",
              "k_seg_count", "k_seg_write"],

@@ -5,24 +5,31 @@
 // skew: under Zipf lookups a few table rows own tens of thousands of pairs.
 // Segments under kLongSegment pairs are short; the others are long.
 //
-//  k_backward_short  short segments: lane groups exactly as the forward.
-//  k_backward_long   long segments (no workspace): workgroups scan ranges of
-//                    segments for long ones.
-//  k_backward_list   long segments (workspace): persistent workgroups take
-//                    work items -- (long segment, part) or (piece of a split
-//                    segment, part) -- from lists the short kernel builds.
-//
-// A long segment (or piece) is summed by one workgroup per 64-column part:
-// four producer wavefronts gather the rows into a ring of LDS buffers with
-// 16-byte loads, and one consumer wavefront (one column per lane) runs the
-// ordered adds out of LDS, so the chain never waits behind load issue.
+// With a workspace (two launches):
+//  k_backward_list   scans the segment offsets and lists the long segments,
+//                    and the pieces of the split ones.
+//  k_backward_rows   its first workgroups run the listed chains, one per
+//                    wavefront or, the longest and the pieces, per workgroup;
+//                    the others run the short segments, a lane group each,
+//                    exactly as the forward. The chains are bound by the
+//                    latency of their gathers and the short segments by
+//                    bandwidth, so they overlap.
+// Without one, every segment is one chain of any length, and the longest
+// sets the time:
+//  k_backward_short  the short segments.
+//  k_backward_long   workgroups scan ranges of segments for long ones and run
+//                    each with four producer wavefronts that gather the rows
+//                    into a ring of LDS buffers with 16-byte loads and one
+//                    consumer wavefront (one column per lane) that runs the
+//                    ordered adds out of LDS, so the chain never waits behind
+//                    load issue.
 //
 // Summation order. Without a workspace every segment is one ordered chain
 // from +0, the sequential definition bit for bit. With a workspace that
 // covers them, segments of kSplitPairs pairs or more are cut into n =
 // min(kMaxPieces, len / kPieceMin) pieces of consecutive pairs; each piece is
-// an ordered chain from +0 run by its own work item, which stores the piece
-// sum, and the item that finishes a segment's last piece (an agent-scope
+// an ordered chain from +0 of its own, whose last wavefront stores the piece
+// sum, and the one that finishes a segment's last piece (an agent-scope
 // counter per segment and part) adds the n piece sums in piece order from
 // +0. The order is fixed by the segment's length alone, so results do not
 // depend on scheduling and repeat bit for bit; the chain of the hottest row
@@ -70,43 +77,58 @@ constexpr int kLongRanges = 1024;
 constexpr int32_t kSplitPairs = TC_BACKWARD_SPLIT_PAIRS;
 constexpr int32_t kPieceMin = 1024;
 constexpr int32_t kMaxPieces = 32;
-static_assert(kSplitPairs >= 2 * kPieceMin && kPieceMin >= kLongSegment, "piece sizes");
-// Long segments of at least kBigLong pairs are handed out before the shorter
-// ones, so that the work left at the end is small (the workgroups finish
-// together).
+// Long segments of at least kBigLong pairs, and pieces, are chains of a whole
+// workgroup (about 5 ns per row), which end soon enough not to outlast the
+// short segments; the shorter ones of a wavefront (17 ns), which holds a
+// quarter of the workgroup's slots while the chain starts and ends.
 constexpr int32_t kBigLong = 512;
+static_assert(kPieceMin >= kBigLong && kBigLong > kLongSegment, "list entries");
+static_assert(kSplitPairs >= 2 * kPieceMin && kPieceMin >= kLongSegment, "piece sizes");
+// Workgroups of k_backward_list: kListBlocks, or kListBlocksSmall when the
+// workspace is too small to hold more heads.
+constexpr int kListBlocks = 256;
+constexpr int kListBlocksSmall = 16;
+// Cost of a segment outside the chains, in pairs of a chain (k_backward_rows).
+constexpr float kSegmentCost = 12.f;
+constexpr int kXcds = 8;
 
-// The backward workspace. The lists are filled by k_backward_short and
-// drained by k_backward_list; k_backward_init zeroes the counters first.
-// A long segment [beg, beg + len) is covered when beg + len <= cap_pairs and
-// split when also len >= kSplitPairs. Split segments are disjoint intervals
-// of at least kSplitPairs pairs, and pieces of at least kPieceMin pairs, so
-// beg / kSplitPairs and (first pair of the piece) / kPieceMin name them
-// without collisions.
-//   ctr[0]           entries in pieces[]
-//   ctr[1], ctr[2]   long segments of at least / under kBigLong pairs, kept
-//                    from the front / from the back of longs[]
-//   ctr[3]           next work item
-//   pieces[k]        {u, beg, len, q}: piece q of split segment u
-//   longs[k]         {u, beg, len, 0}: a covered long segment, not split
+// The backward workspace, written by k_backward_list and read by
+// k_backward_rows. A long segment [beg, beg + len) is covered when beg + len
+// <= cap_pairs and split when also len >= kSplitPairs.
+// Workgroup b of the list kernel scans a range of consecutive segments, that
+// is the pairs [P0, P1), and keeps its entries in slots of its own, with no
+// counter shared between workgroups to clear first: an entry of big[] stands
+// for at least kBigLong pairs, so [P0 / kBigLong, P1 / kBigLong) holds all of
+// them, and one of longs[] for at least kLongSegment.
+//   heads[b]   {entries in big[], entries in longs[], P0, pairs of its long
+//              segments}, zeros past the workgroups launched
+//   big[k]     {u, q}: piece q of split segment u, or with q < 0 a segment of
+//              at least kBigLong pairs that is not split
+//   longs[k]   {u, beg}: a shorter long segment
+// Split segments are disjoint intervals of at least kSplitPairs pairs, and
+// pieces of at least kPieceMin pairs, so beg / kSplitPairs and (first pair of
+// the piece) / kPieceMin name them without collisions:
 //   seg_done[(beg / kSplitPairs) * parts + p]  pieces of part p finished
 //   partial[(first pair / kPieceMin) * dim + c]  piece sums
 struct SplitWs {
-    int32_t *ctr;
-    int4 *pieces;
-    int4 *longs;
+    int4 *heads;
+    int2 *big;
+    int2 *longs;
     int32_t *seg_done;
     float *partial;
     int64_t cap_pairs;  // 0: no workspace
-    int32_t max_pieces, max_longs;
+    int32_t list_blocks;
     int32_t parts;
 };
 
 __device__ __forceinline__ int32_t num_pieces(int32_t len) {
     return len / kPieceMin < kMaxPieces ? len / kPieceMin : kMaxPieces;
 }
+// beg + floor(q * len / n), without the 64-bit division (about 170 instructions):
+// with len = n * a + b, floor(q * len / n) = q * a + floor(q * b / n).
 __device__ __forceinline__ int32_t piece_begin(int32_t beg, int32_t len, int32_t n, int32_t q) {
-    return beg + int32_t(int64_t(q) * len / n);
+    const uint32_t a = uint32_t(len) / uint32_t(n), b = uint32_t(len) - a * uint32_t(n);
+    return beg + int32_t(uint32_t(q) * a + uint32_t(q) * b / uint32_t(n));
 }
 
 // Buffer resource word 3 for gfx9-family buffers; out-of-range reads give 0.
@@ -437,29 +459,41 @@ __device__ __forceinline__ float run_chain(LongLds &lds, const float *__restrict
     return 0.f;
 }
 
-// Consumer wavefront, after piece q of split segment u: store the piece sum,
+// Wavefront that summed piece q of split segment u: store the piece sum,
 // count the piece, and if it was the segment's last (for this part), add the
-// n piece sums in piece order from +0 and hand the row to the sink.
-__device__ void finish_piece(const SplitWs &ws, const RowSink &sink, int32_t dim, int32_t part,
-                             int32_t col, int32_t u, int32_t beg, int32_t len, int32_t n,
-                             int32_t q, float acc) {
+// n piece sums in piece order from +0 and hand the row to the sink. The piece
+// sums and counts are agent-scope atomics throughout, so a wait between the
+// store and the count orders them for every XCD; a fence at agent scope would
+// write back and invalidate the whole L2 of the XCD for each piece. The n
+// sums are loaded all at once: one after another they would end the call with
+// up to 32 round trips.
+__device__ __forceinline__ void finish_piece(const SplitWs &ws, const RowSink &sink, int32_t dim,
+                                             int32_t part, int32_t col, int32_t u, int32_t beg,
+                                             int32_t len, int32_t n, int32_t q, float acc) {
     const int lane = threadIdx.x & (kWave - 1);
+    float *sums = ws.partial + (col < dim ? col : 0);
     if (col < dim)
-        ws.partial[int64_t(piece_begin(beg, len, n, q) / kPieceMin) * dim + col] = acc;
-    // the piece sum reaches device scope before the count does
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __hip_atomic_store(sums + int64_t(piece_begin(beg, len, n, q) / kPieceMin) * dim, acc,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // for the compiler
+    __builtin_amdgcn_s_waitcnt(0);
     int32_t done = 0;
     if (lane == 0)
         done = __hip_atomic_fetch_add(&ws.seg_done[int64_t(beg / kSplitPairs) * ws.parts + part],
                                       1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     done = __builtin_amdgcn_readlane(done, 0);
     if (done != n - 1) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (col >= dim) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int32_t at = piece_begin(beg, len, n, min(lane, n - 1)) / kPieceMin;  // of piece `lane`
+    float x[kMaxPieces];
+#pragma unroll
+    for (int k = 0; k < kMaxPieces; ++k)
+        x[k] = __hip_atomic_load(sums + int64_t(__builtin_amdgcn_readlane(at, k)) * dim,
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     float tot = 0.f;
-    for (int32_t k = 0; k < n; ++k)
-        tot = tot + ws.partial[int64_t(piece_begin(beg, len, n, k) / kPieceMin) * dim + col];
-    sink_value(sink, u, dim, col, tot, sink_value_load(sink, u, dim, col));
+#pragma unroll
+    for (int k = 0; k < kMaxPieces; ++k) tot = k < n ? tot + x[k] : tot;
+    if (col < dim) sink_value(sink, u, dim, col, tot, sink_value_load(sink, u, dim, col));
 }
 
 // Long segments without a workspace. Each block (range x, part y) scans a
@@ -517,143 +551,474 @@ __global__ __launch_bounds__(kLongThreads) void k_backward_long(
     }
 }
 
-// Long segments with a workspace: persistent blocks take work items
-// (index / parts = list entry: pieces, then long segments of at least
-// kBigLong pairs, then the shorter ones; index % parts = part) from an
-// agent-scope counter until the lists are drained. The next item and its
-// list entry are fetched while the current one runs.
-__global__ __launch_bounds__(kLongThreads, 3) void k_backward_list(
-    const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids, RowSink sink,
-    SplitWs ws, int32_t grad_bytes) {
-    __shared__ LongLds lds;
-    // the next item and its list entry, in two slots used in turn
-    __shared__ int32_t next_item[2];
-    __shared__ int4 next_entry[2];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int32_t np = min(ws.ctr[0], ws.max_pieces);
-    const int32_t nb = min(ws.ctr[1], ws.max_longs);
-    const int32_t ns = min(ws.ctr[2], ws.max_longs - nb);
-    const int64_t total = int64_t(np + nb + ns) * ws.parts;
-    if (total == 0) return;  // uniform: nothing listed (no segment is long)
-    // thread 0: take the next item and load its list entry into slot s
-    auto take = [&](int s) {
-        const int32_t i = __hip_atomic_fetch_add(&ws.ctr[3], 1, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-        next_item[s] = i;
-        if (i < total) {
-            const int32_t k = i / ws.parts;
-            next_entry[s] = k < np        ? ws.pieces[k]
-                            : k < np + nb ? ws.longs[k - np]
-                                          : ws.longs[ws.max_longs - 1 - (k - np - nb)];
+// Lists the long segments, in an order of no consequence. Only segments inside the cover matter, and each
+// has at least one pair, so the first cap_pairs segments hold all of them.
+constexpr int kListThreads = 1024;
+__global__ __launch_bounds__(kListThreads) void k_backward_list(
+    const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
+    int64_t num_out_cap, SplitWs ws) {
+    __shared__ int32_t count[3];  // entries in big[], in longs[], pairs in both
+    const int64_t u_dev = *num_out_dev;
+    int64_t num = u_dev < num_out_cap ? u_dev : num_out_cap;
+    num = num < ws.cap_pairs ? num : ws.cap_pairs;
+    // Ranges of equal size; of the capacity's segments where that leaves each
+    // thread one, so that the offsets are read beside num, not after it.
+    const int64_t most = min(num_out_cap, ws.cap_pairs);
+    const bool one_each = most <= int64_t(gridDim.x) * kListThreads;
+    const int64_t per = ((one_each ? most : num) + gridDim.x - 1) / gridDim.x;
+    const int64_t s0 = min(int64_t(blockIdx.x) * per, one_each ? most - 1 : num);
+    const int64_t s1 = min(s0 + per, num);
+    int32_t p0 = one_each || s0 < s1 ? offsets[s0] : 0;
+    if (threadIdx.x < 3) count[threadIdx.x] = 0;
+    __syncthreads();
+    const int32_t big0 = p0 / kBigLong, long0 = p0 / kLongSegment;
+    auto list = [&](int64_t o, int32_t beg, int32_t len) {
+        if (len < kLongSegment || int64_t(beg) + len > ws.cap_pairs) return;
+        atomicAdd(&count[2], len);
+        if (len < kBigLong) {
+            ws.longs[long0 + atomicAdd(&count[1], 1)] = make_int2(int32_t(o), beg);
+        } else if (len < kSplitPairs) {
+            ws.big[big0 + atomicAdd(&count[0], 1)] = make_int2(int32_t(o), -1);
+        } else {
+            const int32_t n = num_pieces(len);
+            int2 *at = ws.big + big0 + atomicAdd(&count[0], n);
+            for (int32_t q = 0; q < n; ++q) at[q] = make_int2(int32_t(o), q);
+            int32_t *done = ws.seg_done + int64_t(beg / kSplitPairs) * ws.parts;
+            for (int32_t p = 0; p < ws.parts; ++p) done[p] = 0;
         }
     };
-    if (threadIdx.x == 0) take(0);
-    lds_barrier();
-    int slot = 0;
-    int32_t item = next_item[0];
-    if (w == 0) __builtin_amdgcn_s_setprio(3);
-    while (item < total) {
-        const int4 e = next_entry[slot];
-        // the item after this one, visible after this item's last barrier
-        if (threadIdx.x == 0) take(slot ^ 1);
-        const int32_t k = item / ws.parts, part = item % ws.parts;
-        const int32_t col = part * kPartCols + lane;
-        const int32_t u = __builtin_amdgcn_readfirstlane(e.x);
-        const int32_t beg = __builtin_amdgcn_readfirstlane(e.y);
-        const int32_t len = __builtin_amdgcn_readfirstlane(e.z);
-        if (k < np) {
-            const int32_t q = __builtin_amdgcn_readfirstlane(e.w);
-            const int32_t n = num_pieces(len);
-            const int32_t p0 = piece_begin(beg, len, n, q);
-            const int32_t p1 = piece_begin(beg, len, n, q + 1);
-            const float acc =
-                run_chain(lds, grad, dim, ids, p0, p1 - p0, w, part, col, grad_bytes);
-            if (w == 0) finish_piece(ws, sink, dim, part, col, u, beg, len, n, q, acc);
-        } else {
-            SinkVal sv{0, 0.f, 0.f};
-            if (w == 0) sv = sink_value_load(sink, u, dim, col);
-            const float acc = run_chain(lds, grad, dim, ids, beg, len, w, part, col, grad_bytes);
-            if (w == 0 && col < dim) sink_value(sink, u, dim, col, acc, sv);
+    // four segments per thread and trip, all their loads before any is used
+    constexpr int kPer = 4;
+    if (one_each) {
+        const int64_t o = min(s0 + threadIdx.x, most - 1);
+        const int32_t beg = offsets[o], end = offsets[o + 1];
+        if (s0 + threadIdx.x < s1) list(o, beg, end - beg);
+    } else {
+        for (int64_t o0 = s0 + threadIdx.x; o0 < s1; o0 += kPer * kListThreads) {
+            int32_t beg[kPer], end[kPer];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const int64_t o = min(o0 + k * kListThreads, s1 - 1);
+                beg[k] = offsets[o];
+                end[k] = offsets[o + 1];
+            }
+#pragma unroll
+            for (int k = 0; k < kPer; ++k)
+                if (o0 + k * kListThreads < s1)
+                    list(o0 + k * kListThreads, beg[k], end[k] - beg[k]);
         }
-        lds_barrier();  // every wavefront is past this item
-        slot ^= 1;
-        item = next_item[slot];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) ws.heads[blockIdx.x] = make_int4(count[0], count[1], p0, count[2]);
+    if (blockIdx.x == 0 && gridDim.x + threadIdx.x < ws.list_blocks)
+        ws.heads[gridDim.x + threadIdx.x] = make_int4(0, 0, 0, 0);
+}
+
+// The ordered chain over ids[beg, beg + len) for one wavefront, lane l owning
+// column l of the part: kDepth row loads of 4 bytes per lane are in flight,
+// one register each; each is added and replaced by the load of the row kDepth
+// further on. Ids come kDepth at a time, one per lane, a round ahead, and are
+// turned into byte offsets there; a row's offset is then one v_readlane into
+// the load's scalar offset. Rows past the end are read as the last one again
+// (a cache hit) and not added. `last()` is called when the last rows are on
+// their way.
+// What bounds it is the gathers' latency: about 700 ns / kDepth = 17 ns per
+// row, with the chains of up to 32 wavefronts on a CU at once. 40 rows are
+// what fits the 64 registers that the short segments' 8 wavefronts per SIMD
+// allow (48 spill, and slow those down). Measured on chains alone (D = 128,
+// 8192 of 100 rows over 16384 bags): 43 us, against 248 us with the chains one
+// after another in five-wavefront workgroups like k_backward_long's, whose
+// start-up each chain then pays by itself.
+constexpr int kDepth = 40;
+static_assert(kDepth % 8 == 0 && kDepth <= kWave && kLongSegment > kDepth, "chain rounds");
+template <class Last>
+__device__ __forceinline__ float wave_chain(const float *__restrict__ grad, int32_t dim,
+                                            const int32_t *__restrict__ ids, int32_t beg,
+                                            int32_t len, int32_t part, int32_t grad_bytes,
+                                            Last &&last) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t col = part * kPartCols + lane;
+    const int32_t row_bytes = dim * 4;
+    const int32_t *sid = ids + beg;
+    int32_t first = 0;
+    uint64_t span = uint64_t(grad_bytes);
+    if (grad_bytes == 0) {  // uniform
+        // ids within a segment are non-decreasing (stable cast order)
+        first = __builtin_amdgcn_readfirstlane(sid[0]);
+        const int32_t end = __builtin_amdgcn_readfirstlane(sid[len - 1]);
+        span = uint64_t(end - first + 1) * uint64_t(row_bytes);
+    }
+    float acc = 0.f;
+    if (span > uint64_t(kOutOfRange) || len >= (1 << 28)) {
+        // as in run_chain: 64-bit addresses
+        last();
+        const float *colp = grad + (col < dim ? col : dim - 1);
+        for (int32_t k = 0; k < len; ++k) acc = acc + colp[int64_t(sid[k]) * dim];
+        return acc;
+    }
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(grad + int64_t(first) * dim), 0, int32_t(span), kBufferWord3);
+    // lanes past the row's columns read its last one (a row's offset, in the
+    // scalar offset, is not range-checked)
+    const int32_t lane_bytes = min(col, dim - 1) * 4;
+    // ids of rows r + lane, rows past the end being the last one
+    auto load_ids = [&](int32_t r) -> int32_t { return sid[min(r + lane, len - 1)]; };
+    auto load = [&](int32_t offs) -> float {
+        return __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_bytes, offs, 0));
+    };
+    // The barriers hold the order of the instructions: an add, then the load
+    // into the same register, so that kDepth registers do for the rows and
+    // each add waits for its own row only.
+    float row[kDepth];
+    int32_t offs = load_ids(0), next_ids = load_ids(kDepth);
+    __builtin_amdgcn_sched_barrier(0);
+    offs = (offs - first) * row_bytes;
+#pragma unroll
+    for (int k = 0; k < kDepth; ++k) {
+        row[k] = load(__builtin_amdgcn_readlane(offs, k));
+        if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
+    int32_t r = kDepth;  // rows loaded; a chain has more
+    do {
+        offs = (next_ids - first) * row_bytes;
+        r += kDepth;
+        next_ids = load_ids(r);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < kDepth; k += 4) {
+            int32_t o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_readlane(offs, k + i);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc = acc + row[k + i];
+                __builtin_amdgcn_sched_barrier(0);
+                row[k + i] = load(o[i]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } while (r < len);
+    last();
+    const int32_t rem = len - (r - kDepth);  // rows of the last round
+#pragma unroll
+    for (int k = 0; k < kDepth; ++k) acc = k < rem ? acc + row[k] : acc;
+    return acc;
+}
+
+// The ordered chain over ids[beg, beg + len) for a whole workgroup: its four
+// wavefronts take groups of kGroupRows rows in turn, each holding the rows of
+// its next group in registers while the others add theirs, and hand the sum
+// on through LDS, one barrier per group. Only a group's adds and the hand-over
+// are in the chain, about 5 ns per row (one chain of 2000 rows: 18 us for the
+// call, 31 us in one wavefront); four groups are in flight. Returns the sum
+// of column `part * kPartCols + lane` in the last wavefront. Every wavefront
+// executes the same number of barriers. Rows past the end read as +0.0 from an
+// out-of-range offset, as in run_chain.
+constexpr int kGroupRows = 40;
+constexpr int kWgWaves = kBlock / kWave;
+static_assert(kGroupRows == 40 && kWgWaves == 4, "a group's loads are in three parts");
+__device__ __forceinline__ float block_chain(float (&hand)[kWave], const float *__restrict__ grad,
+                                             int32_t dim, const int32_t *__restrict__ ids,
+                                             int32_t beg, int32_t len, int w, int32_t part,
+                                             int32_t grad_bytes) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t col = part * kPartCols + lane;
+    const int32_t row_bytes = dim * 4;
+    const int32_t *sid = ids + beg;
+    int32_t first = 0;
+    uint64_t span = uint64_t(grad_bytes);
+    if (grad_bytes == 0) {  // uniform
+        first = __builtin_amdgcn_readfirstlane(sid[0]);
+        const int32_t last = __builtin_amdgcn_readfirstlane(sid[len - 1]);
+        span = uint64_t(last - first + 1) * uint64_t(row_bytes);
+    }
+    float acc = 0.f;
+    if (span > uint64_t(kOutOfRange) || len >= (1 << 28)) {
+        // as in run_chain: 64-bit addresses, one wavefront, no barriers
+        if (w == kWgWaves - 1) {
+            const float *colp = grad + min(col, dim - 1);
+            for (int32_t k = 0; k < len; ++k) acc = acc + colp[int64_t(sid[k]) * dim];
+        }
+        return acc;
+    }
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(grad + int64_t(first) * dim), 0, int32_t(span), kBufferWord3);
+    const int32_t lane_bytes = min(col, dim - 1) * 4;
+    const int32_t rounds = (len + kWgWaves * kGroupRows - 1) / (kWgWaves * kGroupRows);
+    float row[kGroupRows];
+    // ids of this wavefront's group of round r, one per lane
+    auto load_id = [&](int32_t r) -> int32_t {
+        return sid[min((r * kWgWaves + w) * kGroupRows + lane, len - 1)];
+    };
+    auto to_offs = [&](int32_t id, int32_t r) -> int32_t {
+        return (r * kWgWaves + w) * kGroupRows + lane < len ? (id - first) * row_bytes
+                                                            : kOutOfRange;
+    };
+    // the loads of rows K0 .. K0 + K - 1 of a group
+    auto issue = [&](auto k0s, auto ks, int32_t offs) {
+        constexpr int K0 = decltype(k0s)::value, K = decltype(ks)::value;
+#pragma unroll
+        for (int k = K0; k < K0 + K; k += 4) {
+            int32_t o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_readlane(offs, k + i);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                row[k + i] = __builtin_bit_cast(
+                    float,
+                    __builtin_amdgcn_raw_buffer_load_b32(rsrc, o[i] + lane_bytes, 0, 0));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (w == 0) hand[lane] = 0.f;
+    int32_t id = load_id(0), next_id = load_id(1);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" : "+v"(next_id));  // waited for here, not behind the rows
+    int32_t offs = to_offs(id, 0);
+    issue(Int<0>{}, Int<kGroupRows>{}, offs);
+    lds_barrier();
+    for (int i = 0; i < w; ++i) lds_barrier();
+    // (the loads issued in the last round are all past the end)
+    for (int32_t r = 0; r < rounds; ++r) {
+        acc = hand[lane];
+#pragma unroll
+        for (int k = 0; k < kGroupRows; ++k) acc = acc + row[k];
+        hand[lane] = acc;
+        lds_barrier();
+        offs = to_offs(next_id, r + 1);
+        next_id = load_id(r + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        // a part of the next group's loads in each of the others' turns, so
+        // that none of them waits at its barrier for all of the loads
+        issue(Int<0>{}, Int<16>{}, offs);
+        lds_barrier();
+        issue(Int<16>{}, Int<12>{}, offs);
+        lds_barrier();
+        issue(Int<28>{}, Int<12>{}, offs);
+        lds_barrier();
+    }
+    for (int i = w; i < kWgWaves - 1; ++i) lds_barrier();
+    return acc;
+}
+
+// A list as k_backward_rows finds its way in it: before[b] entries come from
+// the list kernel's workgroups before b, and b's own are in slots first[b] on.
+struct ListIndex {
+    int32_t before[kListBlocks], first[kListBlocks];
+};
+// Inclusive prefix over a wavefront, in DPP adds (no LDS round trips).
+__device__ __forceinline__ int32_t wave_prefix(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+// Exclusive prefixes over the workgroup of N values per thread, and their sums.
+template <int N>
+__device__ __forceinline__ void block_prefix(int32_t (&v)[N], int32_t (&total)[N],
+                                             int32_t (&wave_sum)[kBlock / kWave][N]) {
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    int32_t p[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) p[k] = wave_prefix(v[k]);
+    if (lane == kWave - 1)
+#pragma unroll
+        for (int k = 0; k < N; ++k) wave_sum[w][k] = p[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        v[k] = p[k] - v[k];
+        int32_t tot = 0;
+#pragma unroll
+        for (int i = 0; i < kBlock / kWave; ++i) {
+            if (i < w) v[k] += wave_sum[i][k];
+            tot += wave_sum[i][k];
+        }
+        total[k] = __builtin_amdgcn_readfirstlane(tot);
     }
 }
-
-__global__ void k_backward_init(SplitWs ws) {
-    if (threadIdx.x < 4) ws.ctr[threadIdx.x] = 0;
+// The slot of entry i (below the list's length).
+__device__ __forceinline__ int32_t list_slot(const ListIndex &x, int32_t i) {
+    const int lane = threadIdx.x & (kWave - 1);
+    // the last workgroup with before[b] <= i holds it: 64 of every fourth,
+    // then the four
+    int b = 4 * (63 - __builtin_clzll(__ballot(x.before[4 * lane] <= i)));
+#pragma unroll
+    for (int j = 3; j > 0; --j)
+        if (x.before[b + j] <= i) {
+            b += j;
+            break;
+        }
+    return __builtin_amdgcn_readfirstlane(x.first[b] + i - x.before[b]);
 }
 
-// Short segments: one lane group per segment, as the forward; long ones are
-// left to k_backward_long.
+// One chain, of list entry `slot` of big[] (a whole workgroup) or of longs[]
+// (a wavefront), for the columns of one part.
+__device__ __forceinline__ void run_big(float (&hand)[kWave], const float *__restrict__ grad,
+                                        int32_t dim, const int32_t *__restrict__ ids,
+                                        const int32_t *__restrict__ offsets, const RowSink &sink,
+                                        const SplitWs &ws, int32_t slot, int w, int32_t part,
+                                        int32_t grad_bytes) {
+    const int2 e = ws.big[slot];
+    const int32_t u = __builtin_amdgcn_readfirstlane(e.x);
+    const int32_t q = __builtin_amdgcn_readfirstlane(e.y);
+    const int32_t beg = __builtin_amdgcn_readfirstlane(offsets[u]);
+    const int32_t len = __builtin_amdgcn_readfirstlane(offsets[u + 1]) - beg;
+    const int32_t n = q < 0 ? 1 : num_pieces(len);
+    const int32_t b = q < 0 ? beg : piece_begin(beg, len, n, q);
+    const int32_t l = q < 0 ? len : piece_begin(beg, len, n, q + 1) - b;
+    const float acc = block_chain(hand, grad, dim, ids, b, l, w, part, grad_bytes);
+    if (w != kWgWaves - 1) return;
+    const int32_t col = part * kPartCols + (threadIdx.x & (kWave - 1));
+    if (q >= 0)
+        finish_piece(ws, sink, dim, part, col, u, beg, len, n, q, acc);
+    else if (col < dim)
+        sink_value(sink, u, dim, col, acc, sink_value_load(sink, u, dim, col));
+}
+__device__ __forceinline__ void run_long(const float *__restrict__ grad, int32_t dim,
+                                         const int32_t *__restrict__ ids,
+                                         const int32_t *__restrict__ offsets, const RowSink &sink,
+                                         const SplitWs &ws, int32_t slot, int32_t part,
+                                         int32_t grad_bytes) {
+    const int2 e = ws.longs[slot];
+    const int32_t u = __builtin_amdgcn_readfirstlane(e.x);
+    const int32_t beg = __builtin_amdgcn_readfirstlane(e.y);
+    const int32_t len = __builtin_amdgcn_readfirstlane(offsets[u + 1]) - beg;
+    const int32_t col = part * kPartCols + (threadIdx.x & (kWave - 1));
+    // the table row's value, loaded before the chain's last rows are added
+    SinkVal v{0, 0.f, 0.f};
+    const float acc = wave_chain(grad, dim, ids, beg, len, part, grad_bytes,
+                                 [&] { v = sink_value_load(sink, u, dim, col); });
+    if (col < dim) sink_value(sink, u, dim, col, acc, v);
+}
+
+// Short segments: one lane group per segment, as the forward; wavefront
+// `wave` of `nwave`. Long ones are left to the chains: all of them without a
+// workspace, the covered ones with one (uncovered ones are summed here).
 template <int LANES, int CHUNKS>
-__global__ __launch_bounds__(kBlock) void k_backward_short(
-    const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids,
-    const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
-    int64_t num_out_cap, RowSink sink, SplitWs ws) {
+__device__ __forceinline__ void short_segments(const float *__restrict__ grad, int32_t dim,
+                                               const int32_t *__restrict__ ids,
+                                               const int32_t *__restrict__ offsets, int64_t num,
+                                               const RowSink &sink, int64_t cap_pairs,
+                                               int64_t wave, int64_t nwave) {
     constexpr int kGroups = kWave / LANES;
     const int lane = threadIdx.x & (kWave - 1);
     const int sub = lane & (LANES - 1);
     const int grp = lane / LANES;
-    const int64_t u_dev = *num_out_dev;
-    const int64_t num = u_dev < num_out_cap ? u_dev : num_out_cap;
-    const int64_t wave = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
-    const int64_t nwave = (int64_t(gridDim.x) * blockDim.x) / kWave;
     for (int64_t o0 = wave * kGroups; o0 < num; o0 += nwave * kGroups) {
         const int64_t o = o0 + grp;
         int32_t beg = 0, end = 0;
         bool mine = false;
-        bool listed = false;  // a covered long segment, not split
-        int32_t len = 0;
         int64_t r = 0;  // the table row the sink updates
         if (o < num) {
             beg = offsets[o];
             end = offsets[o + 1];
             if (sink.W) r = sink.rows[o];
-            len = end - beg;
-            const bool covered = len >= kLongSegment && int64_t(beg) + len <= ws.cap_pairs;
-            // without a workspace long segments go to k_backward_long; with
-            // one, covered ones go to the lists and uncovered ones stay here
-            mine = ws.cap_pairs == 0 ? len < kLongSegment : !covered;
-            if (covered && len >= kSplitPairs) {
-                if (sub == 0) {
-                    const int32_t n = num_pieces(len);
-                    const int32_t at = __hip_atomic_fetch_add(
-                        &ws.ctr[0], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    for (int32_t q = 0; q < n && at + q < ws.max_pieces; ++q)
-                        ws.pieces[at + q] = make_int4(int32_t(o), beg, len, q);
-                    const int64_t slot = beg / kSplitPairs;
-                    for (int32_t p = 0; p < ws.parts; ++p) ws.seg_done[slot * ws.parts + p] = 0;
-                }
-            } else {
-                listed = covered && sub == 0;
-            }
+            mine = end - beg < kLongSegment || (cap_pairs != 0 && end > cap_pairs);
             if (!mine) end = beg;
-        }
-        // one counter update per wavefront and list: big ones from the
-        // front of longs[], the others from the back
-#pragma unroll
-        for (int big = 1; big >= 0; --big) {
-            const bool mine_list = listed && (len >= kBigLong) == bool(big);
-            const uint64_t lm = __ballot(mine_list);
-            if (lm == 0) continue;
-            const int leader = __builtin_ctzll(lm);
-            int32_t at = 0;
-            if (lane == leader)
-                at = __hip_atomic_fetch_add(&ws.ctr[big ? 1 : 2], __builtin_popcountll(lm),
-                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            at = __builtin_amdgcn_readlane(at, leader) +
-                 __builtin_popcountll(lm & ((uint64_t(1) << lane) - 1));
-            if (mine_list && at < ws.max_longs)
-                ws.longs[big ? at : ws.max_longs - 1 - at] = make_int4(int32_t(o), beg, len, 0);
         }
         float4 acc[CHUNKS];
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
         group_range_sum<LANES, CHUNKS>(grad, dim, ids, 0, beg, end, sub, acc);
         if (mine) sink_group<LANES, CHUNKS>(sink, o, r, dim, sub, acc);
+    }
+}
+
+template <int LANES, int CHUNKS>
+__global__ __launch_bounds__(kBlock) void k_backward_short(
+    const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids,
+    const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
+    int64_t num_out_cap, RowSink sink) {
+    const int64_t u_dev = *num_out_dev;
+    const int64_t num = u_dev < num_out_cap ? u_dev : num_out_cap;
+    const int64_t wave = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
+    const int64_t nwave = (int64_t(gridDim.x) * blockDim.x) / kWave;
+    short_segments<LANES, CHUNKS>(grad, dim, ids, offsets, num, sink, 0, wave, nwave);
+}
+
+// All segments, with a workspace. The chains take the first workgroups
+// (dispatched first, so that they start at once), big[] before longs[], the
+// others the short segments. Chains of neighbouring segments (of one table,
+// sharing its rows of grad) are put on one XCD, workgroups going round-robin
+// over the XCDs, for the sake of its L2; any other mapping gives the same
+// results. All workgroups are resident at once: more would sweep the short
+// segments in uneven windows (32 tables of 1M x 256: 2.42 ms with half as many
+// workgroups again, 2.14 ms with these).
+// The chains' share of the workgroups is that of their pairs among all work,
+// with kSegmentCost pairs for each segment, so that both parts end together,
+// but at least one workgroup per CU (min_chain_blocks): few long chains are
+// bound by their number of wavefronts. Measured (us, the kernel):
+//   kSegmentCost        4    12    36      min per CU  1/2     1     2
+//   8 x 1M x 64       57.9  55.5  55.6               55.7  55.5  59.3
+//   8 x 5M x 128     134.7 123.3 135.4              121.9 123.3 123.2
+//   1 x 50M x 128      386   385   384                385   385   394
+//   8 x 300k x 128    45.9  44.0  44.2               47.8  44.0  43.2
+// Against the short segments first and the chains after them, in a kernel of
+// five-wavefront workgroups: 82, 178, 402 and 71 us.
+template <int LANES, int CHUNKS>
+__global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : CHUNKS == 2 ? 5 : 2) void k_backward_rows(
+    const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids,
+    const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
+    int64_t num_out_cap, RowSink sink, SplitWs ws, int32_t grad_bytes,
+    int32_t min_chain_blocks) {
+    constexpr int kWaves = kBlock / kWave;
+    static_assert(kBlock == kListBlocks, "one head per thread");
+    __shared__ ListIndex big, longs;
+    __shared__ int32_t wave_sum[kWaves][3];
+    __shared__ float hand[kWave];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t u_dev = *num_out_dev;
+    const int64_t num = u_dev < num_out_cap ? u_dev : num_out_cap;
+    const int t = threadIdx.x;  // the lists' heads, one per thread
+    const int4 h = t < ws.list_blocks ? ws.heads[t] : make_int4(0, 0, 0, 0);
+    int32_t before[3] = {h.x, h.y, h.w}, total[3];
+    block_prefix(before, total, wave_sum);
+    const int32_t nbig = total[0], nlong = total[1], chain_pairs = total[2];
+    big.before[t] = before[0];
+    big.first[t] = h.z / kBigLong;
+    longs.before[t] = before[1];
+    longs.first[t] = h.z / kLongSegment;
+    __syncthreads();
+    // rounds of one workgroup per XCD: an (entry, part) item of big[] is a
+    // workgroup's, one of longs[] a wavefront's
+    const int64_t ibig = int64_t(nbig) * ws.parts, ilong = int64_t(nlong) * ws.parts;
+    const int64_t rbig = (ibig + kXcds - 1) / kXcds;
+    const int64_t rlong = (ilong + kXcds * kWaves - 1) / (kXcds * kWaves);
+    const int64_t rounds = rbig + rlong;
+    const int32_t share = int32_t(float(gridDim.x) * float(chain_pairs) /
+                                  (float(chain_pairs) + kSegmentCost * float(num) + 1.f));
+    const int32_t most = min(max(share, min_chain_blocks), int32_t(gridDim.x) * 7 / 8) / kXcds;
+    const int32_t chain_rounds = int32_t(rounds < most ? rounds : most);
+    const int32_t chain_blocks = chain_rounds * kXcds;
+    if (int32_t(blockIdx.x) >= chain_blocks) {
+        short_segments<LANES, CHUNKS>(
+            grad, dim, ids, offsets, num, sink, ws.cap_pairs,
+            (int64_t(blockIdx.x) - chain_blocks) * kWaves + threadIdx.x / kWave,
+            (int64_t(gridDim.x) - chain_blocks) * kWaves);
+        return;
+    }
+    const int32_t xcd = blockIdx.x % kXcds;
+    for (int64_t rd = blockIdx.x / kXcds; rd < rounds; rd += chain_rounds) {
+        if (rd < rbig) {
+            const int64_t item = xcd * rbig + rd;
+            if (item < ibig)
+                run_big(hand, grad, dim, ids, offsets, sink, ws,
+                        list_slot(big, int32_t(item / ws.parts)), w, int32_t(item % ws.parts),
+                        grad_bytes);
+        } else {
+            const int64_t item = (xcd * rlong + rd - rbig) * kWaves + w;
+            if (item < ilong)
+                run_long(grad, dim, ids, offsets, sink, ws,
+                         list_slot(longs, int32_t(item / ws.parts)), int32_t(item % ws.parts),
+                         grad_bytes);
+        }
     }
 }
 
@@ -714,23 +1079,32 @@ tc_status launch_expand(const float *grad, int32_t dim, const int32_t *bag_offse
     return TC_ERR_UNSUPPORTED;
 }
 
-// The backward workspace's layout for a cover of cap pairs.
+// The backward workspace's layout for a cover of cap pairs. The heads of
+// k_backward_list's workgroups are in the first area when there are few, and
+// behind longs[] when that area (16 bytes for each of the most long segments
+// there can be, of which an entry takes 8) has room for kListBlocks.
 struct WsLayout {
-    size_t ctr, pieces, longs, seg_done, partial, total;
-    int32_t max_pieces, max_longs;
+    size_t heads, big, longs, seg_done, partial, total;
+    int32_t list_blocks;
 };
 WsLayout ws_layout(int64_t cap, int32_t dim) {
     auto al = [](int64_t x) { return size_t((x + 255) & ~int64_t(255)); };
     const int64_t parts = (dim + kPartCols - 1) / kPartCols;
+    // (an entry of big[], one for each kBigLong pairs at most, takes 8 bytes)
+    const int64_t most_pieces = cap / kPieceMin + 1, most_long = cap / kLongSegment + 1;
+    constexpr int64_t kHead = sizeof(int4);
     WsLayout l;
-    l.max_pieces = int32_t(cap / kPieceMin + 1);
-    l.max_longs = int32_t(cap / kLongSegment + 1);
-    l.ctr = 0;
-    l.pieces = l.ctr + al(4 * 4);
-    l.longs = l.pieces + al(int64_t(l.max_pieces) * 16);
-    l.seg_done = l.longs + al(int64_t(l.max_longs) * 16);
+    l.heads = 0;
+    l.big = l.heads + al(kListBlocksSmall * kHead);
+    l.longs = l.big + al(most_pieces * 16);
+    l.seg_done = l.longs + al(most_long * 16);
     l.partial = l.seg_done + al((cap / kSplitPairs + 1) * parts * 4);
-    l.total = l.partial + al(int64_t(l.max_pieces) * dim * 4);
+    l.total = l.partial + al(most_pieces * dim * 4);
+    l.list_blocks = kListBlocksSmall;
+    if (al(most_long * 8) + kListBlocks * kHead <= al(most_long * 16)) {
+        l.heads = l.longs + al(most_long * 8);
+        l.list_blocks = kListBlocks;
+    }
     return l;
 }
 
@@ -738,7 +1112,7 @@ WsLayout ws_layout(int64_t cap, int32_t dim) {
 // whose layout fits; cap 0 (no workspace) if ws is null or not even
 // kLongSegment pairs fit.
 SplitWs make_split_ws(void *ws, size_t bytes, int32_t dim) {
-    SplitWs s{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0,
+    SplitWs s{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0,
               (dim + kPartCols - 1) / kPartCols};
     if (ws == nullptr || ws_layout(kLongSegment, dim).total > bytes) return s;
     int64_t lo = kLongSegment, hi = (int64_t(1) << 31) - 1;
@@ -748,60 +1122,49 @@ SplitWs make_split_ws(void *ws, size_t bytes, int32_t dim) {
     }
     const WsLayout l = ws_layout(lo, dim);
     char *p = static_cast<char *>(ws);
-    s.ctr = reinterpret_cast<int32_t *>(p + l.ctr);
-    s.pieces = reinterpret_cast<int4 *>(p + l.pieces);
-    s.longs = reinterpret_cast<int4 *>(p + l.longs);
+    s.heads = reinterpret_cast<int4 *>(p + l.heads);
+    s.big = reinterpret_cast<int2 *>(p + l.big);
+    s.longs = reinterpret_cast<int2 *>(p + l.longs);
     s.seg_done = reinterpret_cast<int32_t *>(p + l.seg_done);
     s.partial = reinterpret_cast<float *>(p + l.partial);
     s.cap_pairs = lo;
-    s.max_pieces = l.max_pieces;
-    s.max_longs = l.max_longs;
+    s.list_blocks = l.list_blocks;
     return s;
-}
-
-// Workgroups of k_backward_list: as many as can be resident at once on the
-// current device (occupancy query, cached per device).
-int list_blocks() {
-    constexpr int kMaxDevices = 64;
-    static int cached[kMaxDevices] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return device_cus();
-    if (dev < kMaxDevices) {
-        const int c = __atomic_load_n(&cached[dev], __ATOMIC_RELAXED);
-        if (c > 0) return c;
-    }
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_backward_list, kLongThreads,
-                                                     0) != hipSuccess ||
-        per_cu < 1)
-        return device_cus();
-    const int blocks = per_cu * device_cus();
-    if (dev < kMaxDevices) __atomic_store_n(&cached[dev], blocks, __ATOMIC_RELAXED);
-    return blocks;
 }
 
 tc_status launch_backward(const float *grad, int64_t grad_rows, int32_t dim,
                           const int32_t *ids, const int32_t *offsets,
                           const int32_t *num_out_dev, int64_t cap, const RowSink &out,
                           const SplitWs &ws, hipStream_t stream) {
-    // the long chains address rows from the start of grad when it fits in a
+    // the chains address rows from the start of grad when it fits in a
     // 32-bit buffer window with kOutOfRange past its end
     const int64_t gb = grad_rows * int64_t(dim) * 4;
     const int32_t grad_bytes = gb <= kOutOfRange ? int32_t(gb) : 0;
-    if (ws.cap_pairs > 0) {
-        k_backward_init<<<1, kWave, 0, stream>>>(ws);
-        const tc_status st = check_launch("k_backward_init");
-        if (st != TC_OK) return st;
-    }
-    // the short kernel first: it builds the lists
     const RowShape s = row_shape(dim);
     const int64_t rows_per_block = (kBlock / kWave) * (kWave / s.lanes);
     const unsigned grid = grid_for(cap, rows_per_block, int64_t(device_cus()) * 8);
+    unsigned all_blocks = grid;
+    if (ws.cap_pairs > 0) {
+        const int64_t scanned = cap < ws.cap_pairs ? cap : ws.cap_pairs;
+        k_backward_list<<<grid_for(scanned, kListThreads, ws.list_blocks), kListThreads, 0, stream>>>(
+            offsets, num_out_dev, cap, ws);
+        const tc_status st = check_launch("k_backward_list");
+        if (st != TC_OK) return st;
+        // room for the most chains there can be, in whole rounds over the XCDs
+        const int64_t most = (ws.cap_pairs / kLongSegment + 1) * ws.parts;
+        const int64_t rounds = most / kXcds + 2;
+        all_blocks = grid_for(grid + rounds * kXcds, 1, int64_t(device_cus()) * 8);
+    }
     bool launched = false;
 #define TC_BWD_CASE(L, C)                                                                    \
     if (!launched && s.lanes == L && s.chunks == C) {                                        \
-        k_backward_short<L, C><<<grid, kBlock, 0, stream>>>(grad, dim, ids, offsets,          \
-                                                            num_out_dev, cap, out, ws);      \
+        if (ws.cap_pairs > 0)                                                                \
+            k_backward_rows<L, C><<<all_blocks, kBlock, 0, stream>>>(                        \
+                grad, dim, ids, offsets, num_out_dev, cap, out, ws, grad_bytes,              \
+                device_cus());                                                               \
+        else                                                                                 \
+            k_backward_short<L, C><<<grid, kBlock, 0, stream>>>(grad, dim, ids, offsets,     \
+                                                                num_out_dev, cap, out);      \
         launched = true;                                                                     \
     }
     TC_BWD_CASE(1, 1)
@@ -819,13 +1182,8 @@ tc_status launch_backward(const float *grad, int64_t grad_rows, int32_t dim,
         set_error("no backward kernel for dim %d", dim);
         return TC_ERR_UNSUPPORTED;
     }
-    tc_status st = check_launch("k_backward_short");
-    if (st != TC_OK) return st;
-    if (ws.cap_pairs > 0) {
-        k_backward_list<<<list_blocks(), kLongThreads, 0, stream>>>(grad, dim, ids, out, ws,
-                                                                     grad_bytes);
-        return check_launch("k_backward_list");
-    }
+    const tc_status st = check_launch("k_backward_short");
+    if (st != TC_OK || ws.cap_pairs > 0) return st;
     const int parts = (dim + kPartCols - 1) / kPartCols;
     const int ranges = kLongRanges / parts > 64 ? kLongRanges / parts : 64;
     k_backward_long<<<dim3(ranges, parts), kLongThreads, 0, stream>>>(grad, dim, ids, offsets,
