@@ -90,7 +90,6 @@ constexpr int kListBlocks = 256;
 constexpr int kListBlocksSmall = 16;
 // Cost of a segment outside the chains, in pairs of a chain (k_backward_rows).
 constexpr float kSegmentCost = 12.f;
-constexpr int kXcds = 8;
 
 // The backward workspace, written by k_backward_list and read by
 // k_backward_rows. A long segment [beg, beg + len) is covered when beg + len
@@ -809,16 +808,6 @@ __device__ __forceinline__ float block_chain(float (&hand)[kWave], const float *
 struct ListIndex {
     int32_t before[kListBlocks], first[kListBlocks];
 };
-// Inclusive prefix over a wavefront, in DPP adds (no LDS round trips).
-__device__ __forceinline__ int32_t wave_prefix(int32_t v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
-}
 // Exclusive prefixes over the workgroup of N values per thread, and their sums.
 template <int N>
 __device__ __forceinline__ void block_prefix(int32_t (&v)[N], int32_t (&total)[N],

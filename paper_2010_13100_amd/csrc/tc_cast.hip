@@ -1,17 +1,19 @@
 // Tensor Casting (Algorithm 2) on CDNA4.
 //
 //  1. k_build_keys   -- (src, dst) pairs from the bag-major CSR index:
-//                       key = row, value = bag id. Block 0 also writes the
-//                       tile records of the sort segments (below).
+//                       key = row, value = bag id. Also writes the tile
+//                       records of the sort segments (below) and clears the
+//                       group sums of the passes' digit counts.
 //  2. LSD radix sort by key, stable, at most kMaxRadixBits bits per pass over
 //     the key bits that can be set. Each pass is
-//       k_radix_hist    per-tile digit counts (LDS histograms, one per wave)
-//       k_radix_scan    per-digit exclusive scan over tiles (one block/digit)
-//       k_radix_scatter stable scatter: a wave finds the lanes holding equal
-//                       digits with ballots, counts them into its running
-//                       per-digit count in LDS, waves are combined in tile
-//                       order, and the tile is laid out in sorted order in
-//                       LDS and stored in that order.
+//       k_radix_hist    per-tile digit counts (LDS histograms), and their
+//                       sums over full groups of kGroupTiles tiles
+//       k_radix_scatter stable scatter: the tile's place in each digit from
+//                       the counts of the tiles before it; a wave finds the
+//                       lanes holding equal digits with ballots, counts them
+//                       into its running per-digit count in LDS, waves are
+//                       combined in tile order, and the tile is laid out in
+//                       sorted order in LDS and stored in that order.
 //     A pass reads and writes 8 bytes per pair plus a 4-byte read for the
 //     histogram. The last pass writes the values straight into casted_src.
 //  3. Segment build (the scan and cumulative sum of Algorithm 2):
@@ -19,66 +21,78 @@
 //       k_seg_write  casted_dst, unique_rows, seg_offsets, *num_unique (each
 //                    block sums the head counts of the tiles before it)
 //
+// What bounds it at a batch of a million pairs is not bandwidth (a pass moves
+// 20 bytes per pair, 4 us) but the number of launches and, in each, a chain of
+// dependent steps of 4-10 us that every workgroup goes through once: so few
+// passes with wide digits, and no kernel between a histogram and its scatter.
+// Measured (us, the cast's kernels): 8 tables of 1M rows, 1.3M pairs: 49,
+// against 70 with three passes of 7-bit digits over 2048-pair tiles with a
+// scan kernel each; 16 tables, 91k pairs each: 61 against 84; 13 tables, 139k
+// pairs: 32 against 50; one table of 50M rows, 1.6M pairs: 79 against 104;
+// 32 tables, 5.2M pairs (bandwidth: 10-bit digits leave runs of 16 bytes): 111
+// against 145.
+//
 // Sort segments. The pairs of table t are contiguous in the input
 // (bag-major CSR, tables in order) and so are their rows in the output. When
 // the caller bounds the table sizes, each table is sorted on its
 // table-local row, which needs fewer key bits than the global row (32 tables
-// of 2^20 rows: 20 bits, three passes, instead of 25 bits and four), and the
+// of 2^20 rows: 20 bits, two passes, instead of 25 bits and three), and the
 // last pass adds the table's row offset back. A segment is cut into tiles of
-// kTile pairs (its last tile may be short), tiles of all segments are
+// kSortTile pairs (its last tile may be short), tiles of all segments are
 // numbered in segment order, and a digit's position inside its segment comes
-// from the per-digit scan over all tiles minus that scan at the segment's
-// first tile. k_build_keys writes one record per tile (its pair range and its
-// segment's), so a pass kernel finds its tile with a single load. Without a
-// bound there is one segment, all pairs on global rows, and tiles are plain
-// slices of kTile pairs.
+// from the counts of the segment's tiles. The build writes one record per
+// tile (its pair range and its segment's), so a pass kernel finds its tile
+// with a single load. Without a bound there is one segment, all pairs on
+// global rows, and tiles are plain slices of kSortTile pairs.
 //
 // Within a tile, wave w owns positions [w*kWaveSpan, (w+1)*kWaveSpan) and
 // walks them 64 at a time, lane l taking position base + 64*i + l, so tile
-// order = (wave, iteration, lane) order and every pass is stable. No atomics
-// on global memory; nothing here depends on scheduling order.
+// order = (wave, iteration, lane) order and every pass is stable. The only
+// atomics on global memory are the group sums' (whole numbers, whose order
+// does not matter); nothing here depends on scheduling order.
 //
 // tc_embed_forward_cast runs the forward gather-reduce in the cast's
-// launches: k_forward_build (pairs and first-pass digit counts built per
-// tile, then workgroups of the forward; the first pass needs no
-// k_radix_hist) or, for a small batch, beside the one k_cast_small
-// workgroup.
+// launches: k_forward_build (pairs built per tile, then workgroups of the
+// forward) or, for a small batch, beside the one k_cast_small workgroup.
 #include "tc_group_sum.h"
 
 namespace tc {
 namespace {
 
-// Digits of at most 8 bits: with 2048-pair tiles, wider digits cost more
-// per-tile digit bookkeeping (counts written, scanned and read back for every
-// digit of every tile) than the pass they save, at these sizes.
-constexpr int kMaxRadixBits = 8;
-constexpr int kMaxRadix = 1 << kMaxRadixBits;
-constexpr int kSortWaves = kBlock / kWave;        // 4
-constexpr int kItems = 8;                         // positions per lane per tile
-constexpr int kWaveSpan = kWave * kItems;         // 512
-constexpr int kTile = kSortWaves * kWaveSpan;     // 2048
+// Tiles of the sort: kSortThreads threads, kItems positions per lane, digits of
+// up to kMaxRadixBits bits. Wide digits save passes and cost bookkeeping
+// (counts written and read back for every digit of every tile); tiles of 4096
+// pairs carry that and still spread a batch of a million pairs over all CUs,
+// whose wavefronts rank their pairs four SIMDs at a time.
+constexpr int kMaxRadixBits = 11;
+constexpr int kSortThreads = 512;
+constexpr int kItems = 8;
+constexpr int kSortWaves = kSortThreads / kWave;      // 8
+constexpr int kWaveSpan = kWave * kItems;             // 512
+constexpr int kSortTile = kSortWaves * kWaveSpan;     // 4096
+// Full groups of this many tiles of a segment have their digit counts summed.
+constexpr int kGroupTiles = 16;
+// Tiles of the pair build, of kBlock threads.
+constexpr int kTile = kBlock * kItems;                // 2048
 // Table-local sorting for at most this many tables (one thread per table
 // lays the segments out).
 constexpr int kMaxSegTables = kBlock;
 
 __device__ __forceinline__ uint64_t lanemask_lt(int lane) { return (uint64_t(1) << lane) - 1; }
 
-// Block-wide exclusive scan of one value per thread; returns the prefix and
-// writes the block total to *total.
-__device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
-    __shared__ int32_t wsum[kSortWaves];
+// Exclusive scan over a workgroup of one value per thread; returns the prefix
+// and writes the workgroup's total to *total.
+template <int THREADS>
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t *total) {
+    constexpr int kWaves = THREADS / kWave;
+    __shared__ int32_t wsum[kWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int32_t incl = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int32_t o = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += o;
-    }
+    const int32_t incl = wave_prefix(v);
     if (lane == kWave - 1) wsum[w] = incl;
     __syncthreads();
     int32_t wbase = 0, tot = 0;
 #pragma unroll
-    for (int ww = 0; ww < kSortWaves; ++ww) {
+    for (int ww = 0; ww < kWaves; ++ww) {
         const int32_t s = wsum[ww];
         if (ww < w) wbase += s;
         tot += s;
@@ -114,7 +128,7 @@ __device__ int32_t seg_layout(SegLayout &L, const int32_t *__restrict__ bag_offs
         L.rowoff[t] = int32_t(table_row_offset[t]);
     }
     int32_t total;
-    const int32_t ts = block_exclusive_scan((n_t + kTile - 1) / kTile, &total);
+    const int32_t ts = block_scan<kBlock>((n_t + kSortTile - 1) / kSortTile, &total);
     if (t < num_tables) {
         L.tstart[t] = ts;
         L.pstart[t] = p0;
@@ -143,9 +157,9 @@ __device__ TileRec tile_record(const SegLayout &L, int32_t num_tables, int32_t t
         r.next = L.tstart[sg + 1];
         r.pstart = L.pstart[sg];
         r.rowoff = L.rowoff[sg];
-        r.p0 = L.pstart[sg] + (b - r.first) * kTile;
+        r.p0 = L.pstart[sg] + (b - r.first) * kSortTile;
         const int32_t end = L.pstart[sg + 1];
-        r.p1 = r.p0 + kTile < end ? r.p0 + kTile : end;
+        r.p1 = r.p0 + kSortTile < end ? r.p0 + kSortTile : end;
     }
     return r;
 }
@@ -153,106 +167,6 @@ __device__ TileRec tile_record(const SegLayout &L, int32_t num_tables, int32_t t
 // Bag offsets staged per tile by build_tile (a 2048-pair tile spans at most
 // 2048 bags with pairs; more only with bags without pairs between them).
 constexpr int kStageBags = 2048;
-
-// One sort tile's (src, dst) pairs, with the tile's digit counts for the
-// first radix pass (digits key & mask0, counts[digit * tiles + b], as
-// k_radix_hist writes them): keys are table-local rows when `local`, else
-// global rows; values are bag ids (dst), or pair positions when `positions`
-// (an argsort). Pair j's bag comes from a search: the bag holding the tile's
-// first pair by a 64-way search of the segment's bag offsets, then each
-// pair's by binary search of the tile's bag offsets staged in LDS. Tile b
-// has its record from the segment layout (local; workgroup 0 also writes
-// every tile's record) or is pairs [b*kTile, (b+1)*kTile) of one segment.
-__device__ void build_tile(int32_t b, const int32_t *__restrict__ indices,
-                           const int32_t *__restrict__ bag_offsets,
-                           const int64_t *__restrict__ table_row_offset, int64_t num_bags,
-                           int32_t bags_per_table, int32_t num_tables, int32_t n, bool local,
-                           bool positions, TileRec *__restrict__ recs, int32_t tiles,
-                           int32_t *__restrict__ keys, int32_t *__restrict__ vals,
-                           int32_t *__restrict__ counts, uint32_t mask0) {
-    __shared__ SegLayout L;
-    __shared__ int32_t sbo[kStageBags + 1];
-    __shared__ int32_t hist[kSortWaves][kMaxRadix];
-    __shared__ int32_t s_g0;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    TileRec tr{0, 0, 0, 0, 0, 0, -1, 0};
-    int64_t glo = 0, ghi = num_bags;  // the bags of the tile's segment
-    if (local) {
-        const int32_t total = seg_layout(L, bag_offsets, table_row_offset, num_bags,
-                                         bags_per_table, num_tables);
-        if (b == 0)
-            for (int32_t bb = tid; bb < tiles; bb += kBlock)
-                recs[bb] = tile_record(L, num_tables, total, bb);
-        tr = tile_record(L, num_tables, total, b);
-        glo = int64_t(tr.s) * bags_per_table;
-        ghi = glo + bags_per_table;
-    } else if (int64_t(b) * kTile < n) {
-        tr.s = 0;
-        tr.p0 = b * kTile;
-        tr.p1 = tr.p0 + kTile < n ? tr.p0 + kTile : n;
-    }
-    for (int i = tid; i < kSortWaves * kMaxRadix; i += kBlock) (&hist[0][0])[i] = 0;
-    if (tr.s >= 0) {  // uniform
-        const int32_t p0 = tr.p0, p1 = tr.p1;
-        if (w == 0) {
-            // the last bag g in [glo, ghi) with bag_offsets[g] <= p0, the
-            // range narrowed 64-fold per step
-            int64_t lo = glo, hi = ghi;
-            while (hi - lo > 1) {
-                const int64_t step = (hi - lo + kWave - 1) / kWave;
-                const int64_t g = lo + lane * step;
-                const bool le = g < hi && bag_offsets[g] <= p0;
-                const uint64_t m = __ballot(le);
-                const int l = m ? 63 - __builtin_clzll(m) : 0;
-                lo = lo + l * step;
-                hi = lo + step < hi ? lo + step : hi;
-            }
-            if (lane == 0) s_g0 = int32_t(lo);
-        }
-        __syncthreads();
-        const int64_t g0 = s_g0;
-        const int32_t nst = int32_t(ghi - g0 < kStageBags ? ghi - g0 : kStageBags);
-        for (int32_t i = tid; i <= nst; i += kBlock) sbo[i] = bag_offsets[g0 + i];
-        __syncthreads();
-        // whether the staged offsets hold the bag of every pair of the tile
-        const bool staged = g0 + nst == ghi || sbo[nst] >= p1;
-#pragma unroll
-        for (int i = 0; i < kItems; ++i) {
-            const int32_t j = p0 + i * kBlock + tid;
-            if (j < p1) {
-                int64_t g;
-                if (staged) {
-                    int32_t lo = 0, hi = nst - 1;
-                    while (lo < hi) {
-                        const int32_t mid = (lo + hi + 1) / 2;
-                        if (sbo[mid] <= j) lo = mid; else hi = mid - 1;
-                    }
-                    g = g0 + lo;
-                } else {
-                    int64_t lo = g0, hi = ghi - 1;
-                    while (lo < hi) {
-                        const int64_t mid = (lo + hi + 1) / 2;
-                        if (bag_offsets[mid] <= j) lo = mid; else hi = mid - 1;
-                    }
-                    g = lo;
-                }
-                const int32_t idx = indices[j];
-                const int32_t key =
-                    local ? idx : int32_t(table_row_offset[g / bags_per_table] + idx);
-                keys[j] = key;
-                vals[j] = positions ? j : int32_t(g);
-                atomicAdd(&hist[w][uint32_t(key) & mask0], 1);
-            }
-        }
-    }
-    __syncthreads();
-    for (uint32_t d = tid; d <= mask0; d += kBlock) {
-        int32_t c = 0;
-#pragma unroll
-        for (int ww = 0; ww < kSortWaves; ++ww) c += hist[ww][d];
-        counts[int64_t(d) * tiles + b] = c;
-    }
-}
 
 // The records of all num_tile_slots tile slots, written by one workgroup.
 __device__ void write_tile_records(const int32_t *__restrict__ bag_offsets,
@@ -266,19 +180,103 @@ __device__ void write_tile_records(const int32_t *__restrict__ bag_offsets,
         tiles[b] = tile_record(L, num_tables, total, b);
 }
 
+// Where the sort's bookkeeping is, for the kernels before its first pass:
+// tile records to write (null: none) and group sums to clear.
+struct SortPrep {
+    TileRec *recs;
+    int32_t tile_slots;
+    int32_t *groups;
+    int64_t group_words;
+};
+// The share of workgroup `b` of `blocks` in that; workgroup 0 also writes the
+// records.
+__device__ __forceinline__ void prepare_sort(const SortPrep &sp, int64_t b, int64_t blocks,
+                                             const int32_t *__restrict__ bag_offsets,
+                                             const int64_t *__restrict__ table_row_offset,
+                                             int64_t num_bags, int32_t bags_per_table,
+                                             int32_t num_tables) {
+    for (int64_t i = b * kBlock + threadIdx.x; i < sp.group_words; i += blocks * kBlock)
+        sp.groups[i] = 0;
+    if (sp.recs && b == 0)
+        write_tile_records(bag_offsets, table_row_offset, num_bags, bags_per_table, num_tables,
+                           sp.recs, sp.tile_slots);
+}
+
+// The (src, dst) pairs [b*kTile, (b+1)*kTile): keys are table-local rows when
+// `local`, else global rows; values are bag ids (dst). Pair j's bag comes from
+// a search: the bag holding the tile's first pair by a 64-way search of the
+// bag offsets, then each pair's by binary search of the tile's bag offsets
+// staged in LDS.
+__device__ void build_tile(int32_t b, const int32_t *__restrict__ indices,
+                           const int32_t *__restrict__ bag_offsets,
+                           const int64_t *__restrict__ table_row_offset, int64_t num_bags,
+                           int32_t bags_per_table, int32_t n, bool local,
+                           int32_t *__restrict__ keys, int32_t *__restrict__ vals) {
+    __shared__ int32_t sbo[kStageBags + 1];
+    __shared__ int32_t s_g0;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    const int32_t p0 = b * kTile;
+    const int32_t p1 = n - p0 < kTile ? n : p0 + kTile;
+    if (w == 0) {
+        // the last bag g with bag_offsets[g] <= p0, the range narrowed
+        // 64-fold per step
+        int64_t lo = 0, hi = num_bags;
+        while (hi - lo > 1) {
+            const int64_t step = (hi - lo + kWave - 1) / kWave;
+            const int64_t g = lo + lane * step;
+            const bool le = g < hi && bag_offsets[g] <= p0;
+            const uint64_t m = __ballot(le);
+            const int l = m ? 63 - __builtin_clzll(m) : 0;
+            lo = lo + l * step;
+            hi = lo + step < hi ? lo + step : hi;
+        }
+        if (lane == 0) s_g0 = int32_t(lo);
+    }
+    __syncthreads();
+    const int64_t g0 = s_g0;
+    const int32_t nst = int32_t(num_bags - g0 < kStageBags ? num_bags - g0 : kStageBags);
+    for (int32_t i = tid; i <= nst; i += kBlock) sbo[i] = bag_offsets[g0 + i];
+    __syncthreads();
+    // whether the staged offsets hold the bag of every pair of the tile
+    const bool staged = g0 + nst == num_bags || sbo[nst] >= p1;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int32_t j = p0 + i * kBlock + tid;
+        if (j < p1) {
+            int64_t g;
+            if (staged) {
+                int32_t lo = 0, hi = nst - 1;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi + 1) / 2;
+                    if (sbo[mid] <= j) lo = mid; else hi = mid - 1;
+                }
+                g = g0 + lo;
+            } else {
+                int64_t lo = g0, hi = num_bags - 1;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi + 1) / 2;
+                    if (bag_offsets[mid] <= j) lo = mid; else hi = mid - 1;
+                }
+                g = lo;
+            }
+            const int32_t idx = indices[j];
+            keys[j] = local ? idx : int32_t(table_row_offset[g / bags_per_table] + idx);
+            vals[j] = int32_t(g);
+        }
+    }
+}
+
 // (src, dst) pairs by a walk over the bags (tc_cast_index, tc_argsort_rows):
-// one group of 16 lanes per bag writes that bag's pairs; keys and values as
-// in build_tile. With `local`, block 0 also writes the tile records. The
-// first pass then counts its digits with k_radix_hist: on its own, this walk
-// and that count take less time than build_tile's searches.
+// one group of 16 lanes per bag writes that bag's pairs; keys as in
+// build_tile, values bag ids, or pair positions when `positions` (an argsort).
+// On its own this walk takes less time than build_tile's searches.
 __global__ __launch_bounds__(kBlock) void k_build_keys(
     const int32_t *__restrict__ indices, const int32_t *__restrict__ bag_offsets,
     const int64_t *__restrict__ table_row_offset, int64_t num_bags, int32_t bags_per_table,
-    int32_t num_tables, bool local, bool positions, TileRec *__restrict__ tiles,
-    int32_t num_tile_slots, int32_t *__restrict__ keys, int32_t *__restrict__ vals) {
-    if (local && blockIdx.x == 0)
-        write_tile_records(bag_offsets, table_row_offset, num_bags, bags_per_table, num_tables,
-                           tiles, num_tile_slots);
+    int32_t num_tables, bool local, bool positions, SortPrep sp, int32_t *__restrict__ keys,
+    int32_t *__restrict__ vals) {
+    prepare_sort(sp, blockIdx.x, gridDim.x, bag_offsets, table_row_offset, num_bags,
+                 bags_per_table, num_tables);
     constexpr int kLanes = 16;
     const int64_t group = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kLanes;
     const int64_t ngroups = (int64_t(gridDim.x) * blockDim.x) / kLanes;
@@ -293,21 +291,21 @@ __global__ __launch_bounds__(kBlock) void k_build_keys(
     }
 }
 
-// The pair build and the first pass's digit counts (build_tile, one sort
-// tile per workgroup) with the forward gather-reduce in one launch
-// (tc_embed_forward_cast): the first `tiles` workgroups build the tiles,
-// the others run the forward (FL lanes per bag, as k_forward). Both
-// read the index array; the tile workgroups' searches and stores stay out of
-// the forward's chains of dependent loads, and their latency hides behind
-// the forward's.
+// The pair build (build_tile, one tile per workgroup) with the forward
+// gather-reduce in one launch (tc_embed_forward_cast): the first `tiles`
+// workgroups build the tiles, the others run the forward (FL lanes per bag,
+// as k_forward). Both read the index array; the tile workgroups' searches and
+// stores stay out of the forward's chains of dependent loads, and their
+// latency hides behind the forward's.
 template <int FL>
 __global__ __launch_bounds__(kBlock) void k_forward_build(
-    FwdSlice f, int32_t num_tables, int32_t n, bool local, TileRec *__restrict__ recs,
-    int32_t tiles, int32_t *__restrict__ keys, int32_t *__restrict__ vals,
-    int32_t *__restrict__ counts, uint32_t mask0) {
+    FwdSlice f, int32_t num_tables, int32_t n, bool local, SortPrep sp, int32_t tiles,
+    int32_t *__restrict__ keys, int32_t *__restrict__ vals) {
     if (int32_t(blockIdx.x) < tiles) {  // uniform
+        prepare_sort(sp, blockIdx.x, tiles, f.offsets, f.table_row_offset, f.bag_hi,
+                     f.bags_per_table, num_tables);
         build_tile(blockIdx.x, f.ids, f.offsets, f.table_row_offset, f.bag_hi, f.bags_per_table,
-                   num_tables, n, local, false, recs, tiles, keys, vals, counts, mask0);
+                   n, local, keys, vals);
         return;
     }
     constexpr int64_t kWaves = kBlock / kWave;
@@ -315,33 +313,57 @@ __global__ __launch_bounds__(kBlock) void k_forward_build(
                         (int64_t(gridDim.x) - tiles) * kWaves);
 }
 
-// This block's tile: its record (table-local sort) or a plain slice of the
-// n pairs (global sort: one segment, tiles 0 .. ceil(n/kTile)-1).
-__device__ __forceinline__ TileRec tile_of(const TileRec *__restrict__ tiles, int32_t n) {
-    if (tiles) return tiles[blockIdx.x];
-    const int32_t used = (n + kTile - 1) / kTile;
-    const int32_t p0 = int32_t(blockIdx.x) * kTile;
-    TileRec r{0, 0, 0, used, 0, 0, -1, 0};
-    if (p0 < n) {
+// The tile of this workgroup of a pass: consecutive tiles on one XCD
+// (workgroups go round-robin over the XCDs; any mapping gives the same
+// results), so that the short runs that neighbouring tiles write side by side
+// meet in one L2. Measured with 10-bit digits (us): 5.2M pairs 50.3 -> 35.6,
+// 1.3M pairs 15.7 -> 14.2.
+__device__ __forceinline__ int32_t tile_index() {
+    return int32_t(blockIdx.x % kXcds * (gridDim.x / kXcds) + blockIdx.x / kXcds);
+}
+inline unsigned tile_grid(int32_t tiles) { return unsigned((tiles + kXcds - 1) / kXcds * kXcds); }
+
+// Tile b: its record (table-local sort) or a plain slice of the n pairs
+// (global sort: one segment, tiles 0 .. ceil(n/kSortTile)-1); s < 0 past the
+// last tile.
+__device__ __forceinline__ TileRec tile_of(int32_t b, int32_t tiles,
+                                           const TileRec *__restrict__ recs, int32_t n) {
+    TileRec r{0, 0, 0, 0, 0, 0, -1, 0};
+    if (b >= tiles) return r;
+    if (recs) return recs[b];
+    r.next = (n + kSortTile - 1) / kSortTile;
+    if (b < r.next) {
         r.s = 0;
-        r.p0 = p0;
-        r.p1 = p0 + kTile < n ? p0 + kTile : n;
+        r.p0 = b * kSortTile;
+        r.p1 = n - r.p0 < kSortTile ? n : r.p0 + kSortTile;
     }
     return r;
 }
 
-// Lanes of a wavefront whose digit equals this lane's (BITS ballots), among
-// the lanes where ok holds.
+// Lanes of a wavefront whose digit equals this lane's, among the lanes where
+// ok holds. One ballot per digit bit; a lane's mismatches gather as lanes |
+// (ballot ^ its own bit, spread), one three-input operation on each half.
+__device__ __forceinline__ uint32_t add_mismatch(uint32_t lanes, uint32_t ballot, uint32_t mine) {
+    return __builtin_amdgcn_bitop3_b32(ballot, mine, lanes, (0xf0 ^ 0xcc) | 0xaa);
+}
 template <int BITS>
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool ok) {
-    uint64_t peers = __ballot(ok);
+    const uint64_t out = ~__ballot(ok);
+    uint32_t lo = uint32_t(out), hi = uint32_t(out >> 32);
 #pragma unroll
     for (int b = 0; b < BITS; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t m = __ballot(bit);
-        peers &= bit ? m : ~m;
+        uint32_t mine = uint32_t(__builtin_amdgcn_sbfe(int32_t(d), b, 1));
+        asm("" : "+v"(mine));  // else the ballot tests d << (31 - b), one more instruction
+        const uint64_t m = __ballot(mine != 0);
+        lo = add_mismatch(lo, uint32_t(m), mine);
+        hi = add_mismatch(hi, uint32_t(m >> 32), mine);
     }
-    return peers;
+    return ~(uint64_t(hi) << 32 | lo);
+}
+// Lanes of mask below this one.
+__device__ __forceinline__ int32_t count_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0));
 }
 
 // The same with the digit width known only at run time (uniform branches).
@@ -369,295 +391,346 @@ __device__ __forceinline__ bool all_same_digit(uint32_t d, bool ok, uint64_t *ac
 }
 
 // ---------------------------------------------------------------------------
-// 2a. per-tile digit histogram -> counts[digit * tiles + tile]. Every item
-// adds one to its wave's count of its digit (an LDS atomic; the order of
-// the adds does not matter here), except that a wavefront whose items share
-// one digit adds them all at once. Blocks past the last tile write zeros.
+// Digit counts of the tiles: a tile's row of `counts` holds digits 2t and
+// 2t + 1 in one word (a count is at most kSortTile), and a row of `groups`
+// the sums, one word per digit, over a full group of kGroupTiles tiles of one
+// segment, tiles first + 16 g ... first + 16 g + 15. Groups are disjoint runs
+// of 16 tiles, so (their first tile) / 16 names the row.
+
+// 2a. per-tile digit histogram. Every item adds one to its wave's copy of the
+// histogram (an LDS atomic; the order of the adds does not matter here),
+// except that a wavefront whose items share one digit adds them all at once.
 template <int BITS>
-__global__ __launch_bounds__(kBlock) void k_radix_hist(const int32_t *__restrict__ keys,
-                                                       int32_t n, int shift,
-                                                       const TileRec *__restrict__ recs,
-                                                       int32_t *__restrict__ counts,
-                                                       int32_t tiles) {
+__global__ __launch_bounds__(kSortThreads) void k_radix_hist(
+    const int32_t *__restrict__ keys, int32_t n, int shift, const TileRec *__restrict__ recs,
+    int32_t tiles, uint32_t *__restrict__ counts, int32_t *__restrict__ groups) {
     constexpr int R = 1 << BITS;
-    __shared__ int32_t hist[kSortWaves][R];
+    constexpr int kHistCopies = R > 1024 ? 2 : 4;
+    __shared__ int32_t hist[kHistCopies][R];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     constexpr uint32_t mask = R - 1u;
-    const TileRec tr = tile_of(recs, n);
-    const int32_t base = tr.p0 + w * kWaveSpan;
+    for (int i = tid; i < kHistCopies * R; i += kSortThreads) (&hist[0][0])[i] = 0;
+    const int32_t b = tile_index();
+    const TileRec tr = tile_of(b, tiles, recs, n);
+    if (tr.s < 0) return;  // uniform: past the last tile
+    const int32_t in_tile = tr.p1 - tr.p0;  // at least 1
+    const int32_t base = w * kWaveSpan + lane;
+    const int32_t *tile_keys = keys + tr.p0;
     int32_t key[kItems];
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int32_t j = base + i * kWave + lane;
-        key[i] = j < tr.p1 ? keys[j] : 0;
-    }
-    for (int i = tid; i < kSortWaves * R; i += kBlock) (&hist[0][0])[i] = 0;
+    for (int i = 0; i < kItems; ++i)
+        key[i] = tile_keys[uint32_t(min(base + i * kWave, in_tile - 1))];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
-        const bool ok = base + i * kWave + lane < tr.p1;
+        const bool ok = base + i * kWave < in_tile;
         const uint32_t d = (uint32_t(key[i]) >> shift) & mask;
         uint64_t act;
         if (all_same_digit(d, ok, &act)) {
-            if (lane == 0 && act) atomicAdd(&hist[w][d], __popcll(act));
+            if (lane == 0 && act) atomicAdd(&hist[w % kHistCopies][d], __popcll(act));
         } else if (ok) {
-            atomicAdd(&hist[w][d], 1);
+            atomicAdd(&hist[w % kHistCopies][d], 1);
         }
     }
     __syncthreads();
-    for (int d = tid; d < R; d += kBlock) {
-        int32_t s = 0;
+    const int32_t group = tr.first + (b - tr.first) / kGroupTiles * kGroupTiles;
+    const bool full = group + kGroupTiles <= tr.next;
+    for (int t = tid; t < R / 2; t += kSortThreads) {
+        int32_t c[2] = {0, 0};
 #pragma unroll
-        for (int ww = 0; ww < kSortWaves; ++ww) s += hist[ww][d];
-        counts[int64_t(d) * tiles + blockIdx.x] = s;
+        for (int k = 0; k < kHistCopies; ++k) {
+            c[0] += hist[k][2 * t];
+            c[1] += hist[k][2 * t + 1];
+        }
+        counts[int64_t(b) * (R / 2) + t] = uint32_t(c[0]) | uint32_t(c[1]) << 16;
+        if (full) {
+            int32_t *row = groups + int64_t(group / kGroupTiles) * R + 2 * t;
+            if (c[0]) atomicAdd(row, c[0]);
+            if (c[1]) atomicAdd(row + 1, c[1]);
+        }
     }
 }
 
-// 2b. counts[d][*] -> exclusive prefix over tiles (in place); totals[d].
-__global__ __launch_bounds__(kBlock) void k_radix_scan(int32_t *__restrict__ counts,
-                                                       int32_t tiles,
-                                                       int32_t *__restrict__ totals) {
-    constexpr int kPer = 4;
-    int32_t *row = counts + int64_t(blockIdx.x) * tiles;
-    int32_t carry = 0;
-    for (int32_t base = 0; base < tiles; base += kBlock * kPer) {
-        int32_t v[kPer], s = 0;
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int32_t i = base + threadIdx.x * kPer + k;
-            v[k] = i < tiles ? row[i] : 0;
-            s += v[k];
-        }
-        int32_t tot;
-        int32_t p = block_exclusive_scan(s, &tot) + carry;
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int32_t i = base + threadIdx.x * kPer + k;
-            if (i < tiles) row[i] = p;
-            p += v[k];
-        }
-        carry += tot;
-    }
-    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
-}
-
-// 2c. stable scatter of one tile. Within a wavefront the lanes holding equal
-// digits are found with ballots (two if they all share one digit); the lowest of them adds their number to the
-// wave's running count of that digit with one LDS atomic (the returned old
-// value is the count of that digit in earlier items, since a wave's LDS
-// operations complete in order) and the others take it from that lane. The
-// tile is then laid out in sorted order in LDS and written back thread by
-// thread in that order, so neighbouring threads write neighbouring addresses
-// of the same digit run (coalesced stores instead of one scattered store per
-// pair). With add_rowoff the keys leave with the segment's row offset added.
+// 2b. stable scatter of one tile. Where the tile's run of each digit goes
+// comes straight from the counts: the segment's full groups, and at most two
+// partial groups tile by tile, so no scan kernel runs between the histogram
+// and this one, and a segment of any length costs at most its groups and 32
+// loads. Within a wavefront the lanes holding equal digits are found with
+// ballots; each reads the wave's running count of its digit and the lowest of
+// them then adds their number to it. The tile is then laid out in sorted order in LDS, keys and then
+// values, and written back thread by thread in that order, so neighbouring
+// threads write neighbouring addresses of the same digit run (coalesced
+// stores instead of one scattered store per pair). With add_rowoff the keys
+// leave with the segment's row offset added.
 template <int BITS>
-__global__ __launch_bounds__(kBlock) void k_radix_scatter(
+__global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const int32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
     int32_t *__restrict__ keys_out, int32_t *__restrict__ vals_out, int32_t n, int shift,
-    const TileRec *__restrict__ recs, const int32_t *__restrict__ counts,
-    const int32_t *__restrict__ totals, int32_t tiles, bool add_rowoff) {
+    const TileRec *__restrict__ recs, int32_t tiles, const uint32_t *__restrict__ counts,
+    const int32_t *__restrict__ groups, bool add_rowoff) {
     constexpr int R = 1 << BITS;
-    constexpr int DPT = R > kBlock ? R / kBlock : 1;  // digits per thread
+    constexpr int H = R / 2;  // words of two digits
+    constexpr int WPT = H > kSortThreads ? H / kSortThreads : 1;  // consecutive ones per thread
     constexpr uint32_t mask = R - 1u;
-    // wave w's running count of digit d, then the tile-local start of its run
-    __shared__ int32_t wcount[kSortWaves][R];
+    // wave w's running counts, two digits per word, then the tile-local starts
+    // of its runs
+    __shared__ uint32_t wcount[kSortWaves][H];
     __shared__ int32_t run_shift[R];  // global position - tile-local position
-    __shared__ int32_t stage_key[kTile];
-    __shared__ int32_t stage_val[kTile];
+    __shared__ int32_t stage[kSortTile];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    const TileRec tr = tile_of(recs, n);
+    const int32_t b = tile_index();
+    const TileRec tr = tile_of(b, tiles, recs, n);
     if (tr.s < 0) return;  // uniform: past the last tile
 
-    const int32_t base = tr.p0 + w * kWaveSpan;
-    int32_t key[kItems], val[kItems], rank[kItems];
+    const int32_t in_tile = tr.p1 - tr.p0;  // at least 1
+    const int32_t base = w * kWaveSpan + lane;
+    const int32_t *tile_keys = keys_in + tr.p0, *tile_vals = vals_in + tr.p0;
+    int32_t key[kItems], val[kItems];
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int32_t j = base + i * kWave + lane;
-        const bool ok = j < tr.p1;
-        key[i] = ok ? keys_in[j] : 0;
-        val[i] = ok ? vals_in[j] : 0;
-    }
-    // Thread tid handles digits tid*DPT .. tid*DPT+DPT-1 (digit order): where
-    // this tile's run of each digit starts in the output.
-    const int32_t first = tr.first, next = tr.next;
-    int32_t tile_off[DPT], seg_tot[DPT], my = 0;
-#pragma unroll
-    for (int k = 0; k < DPT; ++k) {
-        const int32_t d = tid * DPT + k;
-        tile_off[k] = seg_tot[k] = 0;
-        if (d < R) {
-            const int64_t row = int64_t(d) * tiles;
-            const int32_t at_first = counts[row + first];
-            tile_off[k] = counts[row + blockIdx.x] - at_first;
-            seg_tot[k] = (next < tiles ? counts[row + next] : totals[d]) - at_first;
-        }
-        my += seg_tot[k];
-    }
-    for (int i = tid; i < kSortWaves * R; i += kBlock) (&wcount[0][0])[i] = 0;
-    int32_t digit_base[DPT];
+    for (int i = 0; i < kItems; ++i) key[i] = tile_keys[uint32_t(min(base + i * kWave, in_tile - 1))];
+    for (int i = tid; i < kSortWaves * H; i += kSortThreads) (&wcount[0][0])[i] = 0;
+    // where this tile's runs of the thread's digits start
+    int32_t digit_base[2 * WPT];
     {
-        int32_t tot;
-        int32_t p = block_exclusive_scan(my, &tot) + tr.pstart;
+        int32_t before[2 * WPT], total[2 * WPT], my = 0;
 #pragma unroll
-        for (int k = 0; k < DPT; ++k) {
-            digit_base[k] = p + tile_off[k];
-            p += seg_tot[k];
+        for (int k = 0; k < 2 * WPT; ++k) before[k] = total[k] = 0;
+        if (tid * WPT < H) {
+            const int32_t full = (tr.next - tr.first) / kGroupTiles;  // full groups
+            const int32_t mine = (b - tr.first) / kGroupTiles;
+            for (int32_t g0 = 0; g0 < full; g0 += 8) {
+                int32_t c[8][2 * WPT];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int32_t *row =
+                        groups + int64_t((tr.first + min(g0 + i, full - 1) * kGroupTiles) /
+                                         kGroupTiles) * R;
+#pragma unroll
+                    for (int k = 0; k < 2 * WPT; ++k) c[i][k] = row[uint32_t(2 * WPT * tid + k)];
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int32_t any = g0 + i < full ? -1 : 0, in = g0 + i < mine ? -1 : 0;
+#pragma unroll
+                    for (int k = 0; k < 2 * WPT; ++k) {
+                        total[k] += c[i][k] & any;
+                        before[k] += c[i][k] & in;
+                    }
+                }
+            }
+            // the tiles of this one's group before it, and those past the
+            // full groups (rows past them are read as the last one, and masked)
+            const auto rows = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint32_t *>(counts), 0, -1, 0x00020000);
+            auto add_tiles = [&](int32_t from, int32_t to, int32_t (&sum)[2 * WPT]) {
+#pragma unroll
+                for (int k = 0; k < WPT; ++k) {
+                    uint32_t c[kGroupTiles];
+#pragma unroll
+                    for (int i = 0; i < kGroupTiles; ++i)
+                        c[i] = __builtin_amdgcn_raw_buffer_load_b32(
+                            rows, (tid * WPT + k) * 4,
+                            uint32_t(min(from + i, tr.next - 1)) * uint32_t(H * 4), 0);
+#pragma unroll
+                    for (int i = 0; i < kGroupTiles; ++i) {
+                        c[i] &= from + i < to ? ~0u : 0u;
+                        sum[2 * k] += c[i] & 0xffff, sum[2 * k + 1] += c[i] >> 16;
+                    }
+                }
+            };
+            add_tiles(tr.first + mine * kGroupTiles, b, before);
+            add_tiles(tr.first + full * kGroupTiles, tr.next, total);
+        }
+#pragma unroll
+        for (int k = 0; k < 2 * WPT; ++k) my += total[k];
+        int32_t tot;
+        int32_t p = block_scan<kSortThreads>(my, &tot) + tr.pstart;
+#pragma unroll
+        for (int k = 0; k < 2 * WPT; ++k) {
+            digit_base[k] = p + before[k];
+            p += total[k];
         }
     }
-    __syncthreads();
 
-    // all atomics first, then the broadcasts, so no item waits for the LDS
-    // round trip of the one before it
-    int32_t lower_n[kItems], leader[kItems], old[kItems];
+    // every lane reads its digit's count before the lowest peer adds the item's
+    // to it: a wave's LDS operations complete in order
+    int32_t rank[kItems];
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
-        const bool ok = base + i * kWave + lane < tr.p1;
+        const bool ok = base + i * kWave < in_tile;
         const uint32_t d = (uint32_t(key[i]) >> shift) & mask;
-        uint64_t act;
-        const uint64_t peers = all_same_digit(d, ok, &act) ? act : match_digit<BITS>(d, ok);
-        const uint64_t lower = peers & lanemask_lt(lane);
-        lower_n[i] = __popcll(lower);
-        leader[i] = peers ? __builtin_ctzll(peers) : lane;
-        old[i] = 0;
-        if (ok && lower == 0) old[i] = atomicAdd(&wcount[w][d], __popcll(peers));
+        const uint64_t peers = match_digit<BITS>(d, ok);
+        const int32_t below = count_below(peers);
+        const int sh = 16 * (d & 1);
+        uint32_t *count = &wcount[w][d >> 1];
+        rank[i] = int32_t(__hip_atomic_load(count, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_WAVEFRONT) >> sh & 0xffff) + below;
+        if (ok && below == 0) atomicAdd(count, uint32_t(__popcll(peers)) << sh);
     }
-    // the leader (lowest peer) holds the count of the digit before this item
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) rank[i] = __shfl(old[i], leader[i], kWave) + lower_n[i];
+    for (int i = 0; i < kItems; ++i) val[i] = tile_vals[uint32_t(min(base + i * kWave, in_tile - 1))];
     __syncthreads();
     {
         // per digit: tile-local start of each wave's run (digit order, then
         // wave order) and the shift from tile-local to global positions
-        int32_t c[DPT][kSortWaves], my_n = 0;
+        const bool mine = tid * WPT < H;
+        int32_t sum = 0;
+        if (mine)
 #pragma unroll
-        for (int k = 0; k < DPT; ++k) {
-            const int32_t d = tid * DPT + k;
-#pragma unroll
-            for (int ww = 0; ww < kSortWaves; ++ww) {
-                c[k][ww] = d < R ? wcount[ww][d] : 0;
-                my_n += c[k][ww];
-            }
-        }
-        int32_t tot;
-        int32_t start = block_exclusive_scan(my_n, &tot);
-#pragma unroll
-        for (int k = 0; k < DPT; ++k) {
-            const int32_t d = tid * DPT + k;
-            if (d < R) {
-                run_shift[d] = digit_base[k] - start;
-                int32_t r = start;
+            for (int k = 0; k < WPT; ++k)
 #pragma unroll
                 for (int ww = 0; ww < kSortWaves; ++ww) {
-                    wcount[ww][d] = r;
-                    r += c[k][ww];
+                    const uint32_t c = wcount[ww][tid * WPT + k];
+                    sum += (c & 0xffff) + (c >> 16);
                 }
-                start = r;
+        int32_t tot;
+        int32_t start = block_scan<kSortThreads>(sum, &tot);
+        if (mine)
+#pragma unroll
+            for (int k = 0; k < WPT; ++k) {
+                uint32_t c[kSortWaves];
+                int32_t n0 = 0, n1 = 0;
+#pragma unroll
+                for (int ww = 0; ww < kSortWaves; ++ww) {
+                    c[ww] = wcount[ww][tid * WPT + k];
+                    n0 += c[ww] & 0xffff, n1 += c[ww] >> 16;
+                }
+                int32_t r0 = start, r1 = start + n0;
+                start += n0 + n1;
+                run_shift[2 * (tid * WPT + k)] = digit_base[2 * k] - r0;
+                run_shift[2 * (tid * WPT + k) + 1] = digit_base[2 * k + 1] - r1;
+#pragma unroll
+                for (int ww = 0; ww < kSortWaves; ++ww) {
+                    wcount[ww][tid * WPT + k] = uint32_t(r0) | uint32_t(r1) << 16;
+                    r0 += c[ww] & 0xffff, r1 += c[ww] >> 16;
+                }
             }
-        }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
-        if (base + i * kWave + lane < tr.p1) {
-            const uint32_t d = (uint32_t(key[i]) >> shift) & mask;
-            const int32_t lp = wcount[w][d] + rank[i];
-            stage_key[lp] = key[i];
-            stage_val[lp] = val[i];
-        }
+        const uint32_t d = (uint32_t(key[i]) >> shift) & mask;
+        rank[i] += wcount[w][d >> 1] >> (16 * (d & 1)) & 0xffff;
+        if (base + i * kWave < in_tile) stage[rank[i]] = key[i];
     }
     __syncthreads();
-    const int32_t in_tile = tr.p1 - tr.p0;
     const int32_t koff = add_rowoff ? tr.rowoff : 0;
+    int32_t pos[kItems];
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
-        const int32_t lp = i * kBlock + tid;
+        const int32_t lp = i * kSortThreads + tid;
         if (lp < in_tile) {
-            const int32_t k = stage_key[lp];
-            const uint32_t d = (uint32_t(k) >> shift) & mask;
-            const int32_t pos = run_shift[d] + lp;
-            keys_out[pos] = k + koff;
-            vals_out[pos] = stage_val[lp];
+            const int32_t k = stage[lp];
+            pos[i] = run_shift[(uint32_t(k) >> shift) & mask] + lp;
+            keys_out[pos[i]] = k + koff;
         }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+        if (base + i * kWave < in_tile) stage[rank[i]] = val[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int32_t lp = i * kSortThreads + tid;
+        if (lp < in_tile) vals_out[pos[i]] = stage[lp];
     }
 }
 
 // ---------------------------------------------------------------------------
-// 3a. number of segment heads per tile of the sorted keys.
-__global__ __launch_bounds__(kBlock) void k_seg_count(const int32_t *__restrict__ keys,
-                                                      int64_t n,
-                                                      int32_t *__restrict__ tile_heads) {
-    __shared__ int32_t wsum[kSortWaves];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    const int64_t base = int64_t(blockIdx.x) * kTile + int64_t(w) * kWaveSpan;
-    int32_t c = 0;
-#pragma unroll 4
+// Segment heads of the sorted keys, whose tiles are plain slices of kSortTile:
+// the wavefront's keys (position base + 64 i + lane) and, per i, the lanes
+// whose key differs from its predecessor's.
+struct Heads {
+    int32_t key[kItems];
+    uint64_t lanes[kItems];
+    int32_t count;
+};
+__device__ __forceinline__ Heads segment_heads(const int32_t *__restrict__ keys, int64_t base,
+                                               int64_t n) {
+    Heads h;
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const int64_t j = base + i * kWave + lane;
-        const bool head = j < n && (j == 0 || keys[j] != keys[j - 1]);
-        c += __popcll(__ballot(head));
+        h.key[i] = keys[j < n ? j : n - 1];
     }
-    if (lane == 0) wsum[w] = c;
+    int32_t before = base > 0 && base <= n ? keys[base - 1] : 0;  // the key before item i
+    h.count = 0;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int64_t j = base + i * kWave + lane;
+        // wave_shr:1, lane 0 taking the one before
+        const int32_t prev =
+            __builtin_amdgcn_update_dpp(before, h.key[i], 0x138, 0xf, 0xf, false);
+        h.lanes[i] = __ballot(j < n && (j == 0 || h.key[i] != prev));
+        h.count += __popcll(h.lanes[i]);
+        before = __builtin_amdgcn_readlane(h.key[i], kWave - 1);
+    }
+    return h;
+}
+
+// 3a. number of segment heads per tile.
+__global__ __launch_bounds__(kSortThreads) void k_seg_count(const int32_t *__restrict__ keys,
+                                                            int64_t n, int32_t tiles,
+                                                            int32_t *__restrict__ tile_heads) {
+    __shared__ int32_t wsum[kSortWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    const int32_t b = tile_index();
+    if (b >= tiles) return;  // uniform
+    const Heads h = segment_heads(keys, int64_t(b) * kSortTile + int64_t(w) * kWaveSpan, n);
+    if (lane == 0) wsum[w] = h.count;
     __syncthreads();
     if (tid == 0) {
         int32_t s = 0;
+#pragma unroll
         for (int ww = 0; ww < kSortWaves; ++ww) s += wsum[ww];
-        tile_heads[blockIdx.x] = s;
+        tile_heads[b] = s;
     }
 }
 
 // 3b. casted_dst (inclusive head count - 1), unique_rows and seg_offsets.
 // Each block adds up the head counts of the tiles before it (a few loads per
 // thread even for thousands of tiles, so no separate scan kernel); the last
-// block writes *num_unique.
-__global__ __launch_bounds__(kBlock) void k_seg_write(
-    const int32_t *__restrict__ keys, int64_t n, const int32_t *__restrict__ tile_heads,
-    int32_t *__restrict__ unique_rows, int32_t *__restrict__ seg_offsets,
-    int32_t *__restrict__ casted_dst, int32_t *__restrict__ num_unique) {
+// tile's writes *num_unique.
+__global__ __launch_bounds__(kSortThreads) void k_seg_write(
+    const int32_t *__restrict__ keys, int64_t n, int32_t tiles,
+    const int32_t *__restrict__ tile_heads, int32_t *__restrict__ unique_rows,
+    int32_t *__restrict__ seg_offsets, int32_t *__restrict__ casted_dst,
+    int32_t *__restrict__ num_unique) {
     __shared__ int32_t wsum[kSortWaves];
-    __shared__ int32_t before;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    const int64_t base = int64_t(blockIdx.x) * kTile + int64_t(w) * kWaveSpan;
-    {
-        int32_t part = 0;
-        for (int32_t t = tid; t < int32_t(blockIdx.x); t += kBlock) part += tile_heads[t];
-        int32_t tot;
-        block_exclusive_scan(part, &tot);
-        if (tid == 0) before = tot;
+    const int32_t b = tile_index();
+    if (b >= tiles) return;  // uniform
+    const int64_t base = int64_t(b) * kSortTile + int64_t(w) * kWaveSpan;
+    int32_t part = 0;
+#pragma unroll 4
+    for (int32_t t = tid; t < b; t += kSortThreads) part += tile_heads[t];
+    const Heads h = segment_heads(keys, base, n);
+    if (lane == 0) wsum[w] = h.count;
+    int32_t before;
+    block_scan<kSortThreads>(part, &before);  // (and wsum is written)
+    int32_t run = before, total = before;
+#pragma unroll
+    for (int ww = 0; ww < kSortWaves; ++ww) {
+        if (ww < w) run += wsum[ww];
+        total += wsum[ww];
     }
-    int32_t key[kItems];
-    uint64_t heads[kItems];
-    int32_t c = 0;
+    if (b == tiles - 1 && tid == 0) *num_unique = total;
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const int64_t j = base + i * kWave + lane;
-        key[i] = j < n ? keys[j] : 0;
-        const bool head = j < n && (j == 0 || key[i] != keys[j - 1]);
-        heads[i] = __ballot(head);
-        c += __popcll(heads[i]);
-    }
-    if (lane == 0) wsum[w] = c;
-    __syncthreads();
-    int32_t run = before;
-    for (int ww = 0; ww < w; ++ww) run += wsum[ww];
-    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
-        int32_t total = before;
-        for (int ww = 0; ww < kSortWaves; ++ww) total += wsum[ww];
-        *num_unique = total;
-    }
-    const uint64_t le = lanemask_lt(lane) | (uint64_t(1) << lane);
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int64_t j = base + i * kWave + lane;
-        const int32_t incl = run + __popcll(heads[i] & le);
+        const bool head = h.lanes[i] >> lane & 1u;
+        const int32_t incl = run + count_below(h.lanes[i]) + head;
         if (j < n) {
             if (casted_dst) casted_dst[j] = incl - 1;
-            if ((heads[i] >> lane) & 1u) {
-                unique_rows[incl - 1] = key[i];
+            if (head) {
+                unique_rows[incl - 1] = h.key[i];
                 seg_offsets[incl - 1] = int32_t(j);
             }
             if (j == n - 1) seg_offsets[incl] = int32_t(n);
         }
-        run += __popcll(heads[i]);
+        run += __popcll(h.lanes[i]);
     }
 }
 
@@ -682,31 +755,6 @@ constexpr int kSmallRadix = 1 << kSmallRadixBits;
 static_assert(kSmallRadix <= kSmallThreads, "one digit per thread in the digit scan");
 static_assert(kSmallPairs == kSmallItems * kSmallThreads, "k_cast_small stages one item per trip");
 
-// Block-wide exclusive scan over the kSmallThreads threads.
-__device__ __forceinline__ int32_t small_block_scan(int32_t v, int32_t *total) {
-    __shared__ int32_t wsum[kSmallWaves];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    int32_t incl = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int32_t o = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += o;
-    }
-    if (lane == kWave - 1) wsum[w] = incl;
-    __syncthreads();
-    int32_t wbase = 0, tot = 0;
-#pragma unroll
-    for (int ww = 0; ww < kSmallWaves; ++ww) {
-        const int32_t s = wsum[ww];
-        if (ww < w) wbase += s;
-        tot += s;
-    }
-    __syncthreads();
-    *total = tot;
-    return wbase + incl - v;
-}
-
-//
 // With FL > 0 (tc_embed_forward_cast) the workgroups after the first run the
 // forward gather-reduce beside it, FL lanes per bag: a small cast keeps one
 // CU busy and leaves the others to the forward.
@@ -828,7 +876,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_cast_small(
                 my += c[ww];
             }
             int32_t tot;
-            int32_t r = small_block_scan(my, &tot);
+            int32_t r = block_scan<kSmallThreads>(my, &tot);
             if (tid < kSmallRadix) {
 #pragma unroll
                 for (int ww = 0; ww < kSmallWaves; ++ww) {
@@ -861,7 +909,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_cast_small(
         c += head[i];
     }
     int32_t total;
-    int32_t run = small_block_scan(c, &total);
+    int32_t run = block_scan<kSmallThreads>(c, &total);
 #pragma unroll
     for (int i = 0; i < kSmallItems; ++i) {
         const int32_t j = tid * trips + i;
@@ -890,22 +938,17 @@ __global__ void k_cast_empty(int32_t *seg_offsets, int32_t *num_unique) {
 }
 
 // One LSD pass over `bits` (1..kMaxRadixBits) digit bits starting at `shift`.
-// One radix pass; hist_done: the digit counts are already in `counts` (the
-// first pass, counted by the pair build).
 tc_status launch_radix_pass(int bits, const int32_t *kin, const int32_t *vin, int32_t *kout,
                             int32_t *vout, int32_t n, int shift, const TileRec *recs,
-                            int32_t *counts, int32_t *totals, int32_t tiles, bool last,
-                            bool hist_done, hipStream_t stream) {
+                            uint32_t *counts, int32_t *groups, int32_t tiles, bool last,
+                            hipStream_t stream) {
 #define TC_PASS_CASE(B)                                                                      \
     case B:                                                                                  \
-        if (!hist_done) {                                                                    \
-            k_radix_hist<B><<<tiles, kBlock, 0, stream>>>(kin, n, shift, recs, counts, tiles); \
-            if (check_launch("k_radix_hist") != TC_OK) return TC_ERR_HIP;                    \
-        }                                                                                    \
-        k_radix_scan<<<1 << B, kBlock, 0, stream>>>(counts, tiles, totals);                  \
-        if (check_launch("k_radix_scan") != TC_OK) return TC_ERR_HIP;                        \
-        k_radix_scatter<B><<<tiles, kBlock, 0, stream>>>(kin, vin, kout, vout, n, shift,     \
-                                                         recs, counts, totals, tiles, last); \
+        k_radix_hist<B><<<tile_grid(tiles), kSortThreads, 0, stream>>>(                      \
+            kin, n, shift, recs, tiles, counts, groups);                                     \
+        if (check_launch("k_radix_hist") != TC_OK) return TC_ERR_HIP;                        \
+        k_radix_scatter<B><<<tile_grid(tiles), kSortThreads, 0, stream>>>(                   \
+            kin, vin, kout, vout, n, shift, recs, tiles, counts, groups, last);              \
         return check_launch("k_radix_scatter");
     switch (bits) {
         TC_PASS_CASE(1)
@@ -916,6 +959,9 @@ tc_status launch_radix_pass(int bits, const int32_t *kin, const int32_t *vin, in
         TC_PASS_CASE(6)
         TC_PASS_CASE(7)
         TC_PASS_CASE(8)
+        TC_PASS_CASE(9)
+        TC_PASS_CASE(10)
+        TC_PASS_CASE(11)
         default:
             break;
     }
@@ -923,7 +969,7 @@ tc_status launch_radix_pass(int bits, const int32_t *kin, const int32_t *vin, in
     set_error("no radix pass for %d bits", bits);
     return TC_ERR_UNSUPPORTED;
 }
-static_assert(kMaxRadixBits == 8, "launch_radix_pass instantiates 1..8 bits");
+static_assert(kMaxRadixBits == 11, "launch_radix_pass instantiates 1..11 bits");
 
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -935,27 +981,58 @@ inline int32_t seg_capacity(int32_t num_tables) {
 
 struct CastPlan {
     int64_t sort_tiles;  // tile slots of a radix pass (all segments)
-    int64_t seg_tiles;   // tiles of the segment build (plain tiles of kTile)
-    size_t off_ka, off_va, off_kb, off_vb, off_counts, off_totals, off_heads, off_recs, bytes;
+    int64_t build_tiles, seg_tiles;  // of the pair build (kTile), the segment build (kSortTile)
+    size_t off_ka, off_va, off_kb, off_vb, off_counts, counts_bytes, off_heads, off_recs, bytes;
 };
 
 inline CastPlan cast_plan(int64_t n, int32_t num_tables) {
     CastPlan p{};
     const int32_t nseg = seg_capacity(num_tables);
-    p.seg_tiles = (n + kTile - 1) / kTile;
+    p.build_tiles = (n + kTile - 1) / kTile;
+    p.seg_tiles = (n + kSortTile - 1) / kSortTile;
     p.sort_tiles = p.seg_tiles + nseg;  // each segment adds at most one short tile
     const size_t arr = align_up(size_t(n) * 4);
+    const int64_t slots = p.build_tiles + nseg;
     size_t o = 0;
     p.off_ka = o; o += arr;
     p.off_va = o; o += arr;
     p.off_kb = o; o += arr;
     p.off_vb = o; o += arr;
-    p.off_counts = o; o += align_up(size_t(kMaxRadix) * size_t(p.sort_tiles) * 4);
-    p.off_totals = o; o += align_up(size_t(kMaxRadix) * 4);
-    p.off_heads = o; o += align_up(size_t(p.seg_tiles) * 4);
-    p.off_recs = o; o += align_up(size_t(p.sort_tiles) * sizeof(TileRec));
+    // group sums, and digit counts where the batch's own arrays are too small
+    // for them (sort_digits)
+    p.counts_bytes = align_up(size_t(slots) * 1024) + 1024;
+    p.off_counts = o; o += p.counts_bytes;
+    p.off_heads = o; o += align_up(size_t(p.build_tiles) * 4);
+    p.off_recs = o; o += align_up(size_t(slots) * sizeof(TileRec));
     p.bytes = o;
     return p;
+}
+
+// The passes over `bits` key bits. A pass has counts of a word per two digits
+// and tile, which go where its values are not: the last pass, which writes the
+// values to the caller's array, leaves one of the plan's two value arrays
+// free, and the passes before it the caller's. When the batch is too small for
+// that (n words), as with many more tables than full tiles, they go into the
+// plan's own area. The group sums, one set per pass, are there in any case.
+// The fewest passes that fit are taken; those of 1 bit always do.
+struct SortDigits {
+    int passes, per_pass;
+    bool own_counts;      // counts in the plan's area
+    size_t counts_bytes;  // there, before the group sums
+    size_t group_words;   // of one pass
+};
+inline SortDigits sort_digits(const CastPlan &p, int64_t n, int bits) {
+    SortDigits d{};
+    for (d.passes = (bits + kMaxRadixBits - 1) / kMaxRadixBits;; ++d.passes) {
+        d.per_pass = (bits + d.passes - 1) / d.passes;
+        const size_t radix = size_t(1) << d.per_pass;
+        const size_t counts = size_t(p.sort_tiles) * radix * 2;
+        d.own_counts = counts > size_t(n) * 4;
+        d.counts_bytes = d.own_counts ? align_up(counts) : 0;
+        d.group_words = size_t(p.sort_tiles / kGroupTiles) * radix;
+        if (d.per_pass == 1 || d.counts_bytes + d.passes * d.group_words * 4 <= p.counts_bytes)
+            return d;
+    }
 }
 
 // bits needed for keys in [0, rows)
@@ -1023,8 +1100,6 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
                "%s: workspace of %zu bytes, %zu needed", what, workspace_bytes, plan.bytes);
     TC_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) == 0, TC_ERR_WORKSPACE,
                "%s: workspace must be 256-byte aligned", what);
-    TC_REQUIRE(plan.sort_tiles < (int64_t(1) << 31) / kMaxRadix, TC_ERR_INVALID_ARG,
-               "%s: too many pairs", what);
 
     const int fl = fwd ? ride_along_lanes(fwd->dim) : 0;
     if (fwd && fl == 0) {
@@ -1065,25 +1140,24 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     int32_t *va = reinterpret_cast<int32_t *>(ws + plan.off_va);
     int32_t *kb = reinterpret_cast<int32_t *>(ws + plan.off_kb);
     int32_t *vb = reinterpret_cast<int32_t *>(ws + plan.off_vb);
-    int32_t *counts = reinterpret_cast<int32_t *>(ws + plan.off_counts);
-    int32_t *totals = reinterpret_cast<int32_t *>(ws + plan.off_totals);
     int32_t *heads = reinterpret_cast<int32_t *>(ws + plan.off_heads);
     TileRec *recs = local ? reinterpret_cast<TileRec *>(ws + plan.off_recs) : nullptr;
     const int32_t sort_tiles = int32_t(plan.sort_tiles);
     const int32_t seg_tiles = int32_t(plan.seg_tiles);
+    const int32_t build_tiles = int32_t(plan.build_tiles);
 
-    const int passes = (bits + kMaxRadixBits - 1) / kMaxRadixBits;
-    const int per_pass = (bits + passes - 1) / passes;
-    const uint32_t mask0 = (1u << per_pass) - 1u;  // the first pass's digits
+    const SortDigits digits = sort_digits(plan, num_pairs, bits);
+    const int passes = digits.passes, per_pass = digits.per_pass;
+    int32_t *groups = reinterpret_cast<int32_t *>(ws + plan.off_counts + digits.counts_bytes);
+    const SortPrep prep{recs, sort_tiles, groups, int64_t(digits.group_words) * passes};
     if (fl) {
         // the tiles' pair builds, then the forward's workgroups, in one launch
         const int64_t per_block = int64_t(kBlock / kWave) * (kWave / fl);
         const unsigned grid =
-            unsigned(sort_tiles) + grid_for(num_bags, per_block, int64_t(device_cus()) * 32);
+            unsigned(build_tiles) + grid_for(num_bags, per_block, int64_t(device_cus()) * 32);
 #define TC_FWD_BUILD(FL)                                                                     \
     k_forward_build<FL><<<grid, kBlock, 0, stream>>>(*fwd, num_tables, int32_t(num_pairs),    \
-                                                     local, recs, sort_tiles, ka, va, counts,  \
-                                                     mask0)
+                                                     local, prep, build_tiles, ka, va)
         if (fl == 16) TC_FWD_BUILD(16);
         else if (fl == 32) TC_FWD_BUILD(32);
         else TC_FWD_BUILD(64);
@@ -1094,7 +1168,7 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
         const unsigned grid = grid_for(num_bags, kBlock / 16, int64_t(device_cus()) * 8);
         k_build_keys<<<grid, kBlock, 0, stream>>>(indices, bag_offsets, table_row_offset,
                                                   num_bags, bags_per_table, num_tables, local,
-                                                  positions, recs, sort_tiles, ka, va);
+                                                  positions, prep, ka, va);
         tc_status st = check_launch("k_build_keys");
         if (st != TC_OK) return st;
     }
@@ -1104,9 +1178,12 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
         const int pb = (shift + per_pass <= bits) ? per_pass : bits - shift;
         const bool last = p == passes - 1;
         int32_t *vdst = last ? casted_src : vout;
+        void *counts = digits.own_counts ? ws + plan.off_counts
+                       : last            ? static_cast<void *>(vout)
+                                         : static_cast<void *>(casted_src);
         tc_status st = launch_radix_pass(pb, kin, vin, kout, vdst, int32_t(num_pairs), shift,
-                                         recs, counts, totals, sort_tiles, last,
-                                         p == 0 && fl != 0, stream);
+                                         recs, static_cast<uint32_t *>(counts), groups + p * digits.group_words,
+                                         sort_tiles, last, stream);
         if (st != TC_OK) return st;
         // next pass reads what this one wrote
         int32_t *tk = kin, *tv = vin;
@@ -1117,11 +1194,13 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     }
     const int32_t *sorted_keys = kin;
 
-    k_seg_count<<<seg_tiles, kBlock, 0, stream>>>(sorted_keys, num_pairs, heads);
+    k_seg_count<<<tile_grid(seg_tiles), kSortThreads, 0, stream>>>(sorted_keys, num_pairs,
+                                                                   seg_tiles, heads);
     tc_status st = check_launch("k_seg_count");
     if (st != TC_OK) return st;
-    k_seg_write<<<seg_tiles, kBlock, 0, stream>>>(sorted_keys, num_pairs, heads, unique_rows,
-                                                  seg_offsets, casted_dst, num_unique);
+    k_seg_write<<<tile_grid(seg_tiles), kSortThreads, 0, stream>>>(
+        sorted_keys, num_pairs, seg_tiles, heads, unique_rows, seg_offsets, casted_dst,
+        num_unique);
     return check_launch("k_seg_write");
 }
 }  // namespace

@@ -20,6 +20,8 @@ tc_status check_launch(const char *what);
 constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kBlock = 256;        // threads per block for the streaming kernels
 constexpr int kMaxDim = 1024;
+// XCDs of the chip, each with its own L2; workgroups go round-robin over them.
+constexpr int kXcds = 8;
 
 // Compute units of the current device (hipDeviceGetAttribute, cached per
 // device; 256, an MI355X's count, if the query fails). Grids are sized in
@@ -51,6 +53,17 @@ inline unsigned grid_for(int64_t items, int64_t per_block, int64_t cap_blocks) {
     if (g < 1) g = 1;
     if (g > cap_blocks) g = cap_blocks;
     return static_cast<unsigned>(g);
+}
+
+// Inclusive prefix over a wavefront, in DPP adds (no LDS round trips).
+__device__ __forceinline__ int32_t wave_prefix(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
 }
 
 }  // namespace tc

@@ -1,0 +1,46 @@
+"""The radix cast (more than 8192 pairs) at the sizes where its code changes,
+against the CPU oracle, every index bit for bit: each digit width, pair counts
+around the tile (4096 pairs) and around full groups of 16 tiles, digit counts
+in the batch's own arrays and (more tables than full tiles) in the plan's
+area, and keys that are all equal or all in one digit."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_cast_layouts import check, gpu_cast, oracle_cast
+
+pytestmark = pytest.mark.gpu
+
+TILE, GROUP = 4096, 16
+
+
+# 1..31 key bits: one to three passes of every width of digit
+@pytest.mark.parametrize("bits", [1, 2, 5, 7, 9, 10, 11, 12, 13, 15, 17, 19, 20, 21, 22, 23, 26])
+def test_digit_widths(bits):
+    check(f"{bits} bits", [2 ** bits - (bits > 3)], [3 * TILE - 5], bags_per_table=97, seed=bits,
+          bounds=[0])
+
+
+@pytest.mark.parametrize("tiles", [GROUP - 1, GROUP, GROUP + 1, 2 * GROUP, 3 * GROUP + 1,
+                                   9 * GROUP + 2])
+def test_groups_of_tiles(tiles):
+    n = tiles * TILE
+    check(f"{tiles} tiles", [70_000, 50, 900], [n, n - 1, TILE + 1], bags_per_table=333,
+          seed=tiles)
+
+
+@pytest.mark.parametrize("tables,pairs", [(256, 40), (256, 700), (200, 4097), (37, 230)])
+def test_many_tables(tables, pairs):
+    check(f"{tables} tables", [1000 + 13 * k for k in range(tables)],
+          [pairs + k % 3 for k in range(tables)], bags_per_table=3, seed=tables)
+
+
+@pytest.mark.parametrize("rows,index", [(1, 0), (70_000, 69_999), (2 ** 20, 2 ** 19 + 1)])
+def test_one_row_takes_all(rows, index):
+    n, bags = 17 * TILE + 3, 50
+    off = np.array([0, rows], np.int64)
+    bo = np.linspace(0, n, bags + 1).astype(np.int32)
+    idx = np.full(n, index, np.int32)
+    ref, got = oracle_cast(off, bo, idx, bags), gpu_cast(off, bo, idx, bags, rows)
+    assert got["num_unique"] == ref["num_unique"] == 1
+    for k in ("unique_rows", "seg_offsets", "casted_src", "casted_dst"):
+        assert np.array_equal(got[k], ref[k][:len(got[k])]), k
