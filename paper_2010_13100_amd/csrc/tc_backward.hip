@@ -3,7 +3,8 @@
 // coal_grad[u] is the sum of grad_out rows casted_src[j] over the segment j
 // in [seg_offsets[u], seg_offsets[u+1]). Segment lengths follow the index
 // skew: under Zipf lookups a few table rows own tens of thousands of pairs.
-// Segments under kLongSegment pairs are short; the others are long.
+// Short ones are summed by a lane group, long ones (kListLong pairs with a
+// workspace, kLongSegment without) as chains of their own.
 //
 // With a workspace (two launches):
 //  k_backward_list   scans the segment offsets and lists the long segments,
@@ -48,8 +49,17 @@
 namespace tc {
 namespace {
 
-// Segments at least this long are long.
+// Without a workspace segments at least this long are long; also the fewest
+// pairs that need one.
 constexpr int kLongSegment = 80;
+// With a workspace: a lane group takes 8 rows of a segment per round trip and
+// holds up the wavefront's other groups meanwhile, a chain takes 40 at a time
+// but costs a wavefront's start and end. Measured (us, k_backward_rows) at 80,
+// 64, 48 and 41: 8 x 1M x 64 55.4, 51.5, 49.2, 49.4; 8 x 5M x 128 121.9, 118.8,
+// 117.0, 117.1; 4 x 100k x 512 47.4, 46.8, 43.8, 42.5; 8 x 300k x 128 43.6,
+// 42.0, 42.3, 43.4; 13 ragged x 16 19.6, 18.3, 16.1, 15.6.
+constexpr int kListLong = 48;
+static_assert(kListLong <= kLongSegment, "a workspace covers its long segments");
 // A long-segment workgroup: one consumer and kProducers producer wavefronts.
 constexpr int kProducers = 4;
 constexpr int kLongThreads = (1 + kProducers) * kWave;
@@ -82,7 +92,7 @@ constexpr int32_t kMaxPieces = 32;
 // short segments; the shorter ones of a wavefront (17 ns), which holds a
 // quarter of the workgroup's slots while the chain starts and ends.
 constexpr int32_t kBigLong = 512;
-static_assert(kPieceMin >= kBigLong && kBigLong > kLongSegment, "list entries");
+static_assert(kPieceMin >= kBigLong && kBigLong > kListLong, "list entries");
 static_assert(kSplitPairs >= 2 * kPieceMin && kPieceMin >= kLongSegment, "piece sizes");
 // Workgroups of k_backward_list: kListBlocks, or kListBlocksSmall when the
 // workspace is too small to hold more heads.
@@ -90,6 +100,8 @@ constexpr int kListBlocks = 256;
 constexpr int kListBlocksSmall = 16;
 // Cost of a segment outside the chains, in pairs of a chain (k_backward_rows).
 constexpr float kSegmentCost = 12.f;
+// Cost of a chain beyond its pairs.
+constexpr float kChainCost = 64.f;
 
 // The backward workspace, written by k_backward_list and read by
 // k_backward_rows. A long segment [beg, beg + len) is covered when beg + len
@@ -98,7 +110,7 @@ constexpr float kSegmentCost = 12.f;
 // is the pairs [P0, P1), and keeps its entries in slots of its own, with no
 // counter shared between workgroups to clear first: an entry of big[] stands
 // for at least kBigLong pairs, so [P0 / kBigLong, P1 / kBigLong) holds all of
-// them, and one of longs[] for at least kLongSegment.
+// them, and one of longs[] for at least kListLong.
 //   heads[b]   {entries in big[], entries in longs[], P0, pairs of its long
 //              segments}, zeros past the workgroups launched
 //   big[k]     {u, q}: piece q of split segment u, or with q < 0 a segment of
@@ -570,9 +582,9 @@ __global__ __launch_bounds__(kListThreads) void k_backward_list(
     int32_t p0 = one_each || s0 < s1 ? offsets[s0] : 0;
     if (threadIdx.x < 3) count[threadIdx.x] = 0;
     __syncthreads();
-    const int32_t big0 = p0 / kBigLong, long0 = p0 / kLongSegment;
+    const int32_t big0 = p0 / kBigLong, long0 = p0 / kListLong;
     auto list = [&](int64_t o, int32_t beg, int32_t len) {
-        if (len < kLongSegment || int64_t(beg) + len > ws.cap_pairs) return;
+        if (len < kListLong || int64_t(beg) + len > ws.cap_pairs) return;
         atomicAdd(&count[2], len);
         if (len < kBigLong) {
             ws.longs[long0 + atomicAdd(&count[1], 1)] = make_int2(int32_t(o), beg);
@@ -629,7 +641,7 @@ __global__ __launch_bounds__(kListThreads) void k_backward_list(
 // after another in five-wavefront workgroups like k_backward_long's, whose
 // start-up each chain then pays by itself.
 constexpr int kDepth = 40;
-static_assert(kDepth % 8 == 0 && kDepth <= kWave && kLongSegment > kDepth, "chain rounds");
+static_assert(kDepth % 8 == 0 && kDepth <= kWave && kListLong > kDepth, "chain rounds");
 template <class Last>
 __device__ __forceinline__ float wave_chain(const float *__restrict__ grad, int32_t dim,
                                             const int32_t *__restrict__ ids, int32_t beg,
@@ -909,7 +921,8 @@ __device__ __forceinline__ void short_segments(const float *__restrict__ grad, i
             beg = offsets[o];
             end = offsets[o + 1];
             if (sink.W) r = sink.rows[o];
-            mine = end - beg < kLongSegment || (cap_pairs != 0 && end > cap_pairs);
+            mine = end - beg < (cap_pairs ? kListLong : kLongSegment) ||
+                   (cap_pairs != 0 && end > cap_pairs);
             if (!mine) end = beg;
         }
         float4 acc[CHUNKS];
@@ -941,7 +954,9 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 // segments in uneven windows (32 tables of 1M x 256: 2.42 ms with half as many
 // workgroups again, 2.14 ms with these).
 // The chains' share of the workgroups is that of their pairs among all work,
-// with kSegmentCost pairs for each segment, so that both parts end together,
+// with kSegmentCost pairs for each segment and kChainCost for each chain (8 x
+// 300k x 128, where many chains are short: 49.7 us without), so that both
+// parts end together,
 // but at least one workgroup per CU (min_chain_blocks): few long chains are
 // bound by their number of wavefronts. Measured (us, the kernel):
 //   kSegmentCost        4    12    36      min per CU  1/2     1     2
@@ -973,7 +988,7 @@ __global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : CHUNKS == 2 ? 5 : 2) void
     big.before[t] = before[0];
     big.first[t] = h.z / kBigLong;
     longs.before[t] = before[1];
-    longs.first[t] = h.z / kLongSegment;
+    longs.first[t] = h.z / kListLong;
     __syncthreads();
     // rounds of one workgroup per XCD: an (entry, part) item of big[] is a
     // workgroup's, one of longs[] a wavefront's
@@ -981,8 +996,9 @@ __global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : CHUNKS == 2 ? 5 : 2) void
     const int64_t rbig = (ibig + kXcds - 1) / kXcds;
     const int64_t rlong = (ilong + kXcds * kWaves - 1) / (kXcds * kWaves);
     const int64_t rounds = rbig + rlong;
-    const int32_t share = int32_t(float(gridDim.x) * float(chain_pairs) /
-                                  (float(chain_pairs) + kSegmentCost * float(num) + 1.f));
+    const float chains = float(chain_pairs) + kChainCost * float(nbig + nlong);
+    const int32_t share =
+        int32_t(float(gridDim.x) * chains / (chains + kSegmentCost * float(num) + 1.f));
     const int32_t most = min(max(share, min_chain_blocks), int32_t(gridDim.x) * 7 / 8) / kXcds;
     const int32_t chain_rounds = int32_t(rounds < most ? rounds : most);
     const int32_t chain_blocks = chain_rounds * kXcds;
@@ -1070,8 +1086,9 @@ tc_status launch_expand(const float *grad, int32_t dim, const int32_t *bag_offse
 
 // The backward workspace's layout for a cover of cap pairs. The heads of
 // k_backward_list's workgroups are in the first area when there are few, and
-// behind longs[] when that area (16 bytes for each of the most long segments
-// there can be, of which an entry takes 8) has room for kListBlocks.
+// behind longs[] when that area (16 bytes for each kLongSegment pairs, 8 of
+// which an entry takes for each kListLong) has room for kListBlocks: from
+// about 125 thousand pairs on.
 struct WsLayout {
     size_t heads, big, longs, seg_done, partial, total;
     int32_t list_blocks;
@@ -1080,17 +1097,18 @@ WsLayout ws_layout(int64_t cap, int32_t dim) {
     auto al = [](int64_t x) { return size_t((x + 255) & ~int64_t(255)); };
     const int64_t parts = (dim + kPartCols - 1) / kPartCols;
     // (an entry of big[], one for each kBigLong pairs at most, takes 8 bytes)
-    const int64_t most_pieces = cap / kPieceMin + 1, most_long = cap / kLongSegment + 1;
+    const int64_t most_pieces = cap / kPieceMin + 1, area = cap / kLongSegment + 1;
+    const int64_t most_long = cap / kListLong + 1;
     constexpr int64_t kHead = sizeof(int4);
     WsLayout l;
     l.heads = 0;
     l.big = l.heads + al(kListBlocksSmall * kHead);
     l.longs = l.big + al(most_pieces * 16);
-    l.seg_done = l.longs + al(most_long * 16);
+    l.seg_done = l.longs + al(area * 16);
     l.partial = l.seg_done + al((cap / kSplitPairs + 1) * parts * 4);
     l.total = l.partial + al(most_pieces * dim * 4);
     l.list_blocks = kListBlocksSmall;
-    if (al(most_long * 8) + kListBlocks * kHead <= al(most_long * 16)) {
+    if (al(most_long * 8) + kListBlocks * kHead <= al(area * 16)) {
         l.heads = l.longs + al(most_long * 8);
         l.list_blocks = kListBlocks;
     }
@@ -1140,7 +1158,7 @@ tc_status launch_backward(const float *grad, int64_t grad_rows, int32_t dim,
         const tc_status st = check_launch("k_backward_list");
         if (st != TC_OK) return st;
         // room for the most chains there can be, in whole rounds over the XCDs
-        const int64_t most = (ws.cap_pairs / kLongSegment + 1) * ws.parts;
+        const int64_t most = (ws.cap_pairs / kListLong + 1) * ws.parts;
         const int64_t rounds = most / kXcds + 2;
         all_blocks = grid_for(grid + rounds * kXcds, 1, int64_t(device_cus()) * 8);
     }
