@@ -367,18 +367,20 @@ __device__ __forceinline__ int32_t count_below(uint64_t mask) {
 }
 
 // The same with the digit width known only at run time (uniform branches).
-template <int MAXB = kMaxRadixBits>
 __device__ __forceinline__ uint64_t match_digit_n(uint32_t d, bool ok, int bits) {
-    uint64_t peers = __ballot(ok);
+    const uint64_t out = ~__ballot(ok);
+    uint32_t lo = uint32_t(out), hi = uint32_t(out >> 32);
 #pragma unroll
-    for (int b = 0; b < MAXB; ++b) {
+    for (int b = 0; b < kMaxRadixBits; ++b) {
         if (b < bits) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
+            uint32_t mine = uint32_t(__builtin_amdgcn_sbfe(int32_t(d), b, 1));
+            asm("" : "+v"(mine));
+            const uint64_t m = __ballot(mine != 0);
+            lo = add_mismatch(lo, uint32_t(m), mine);
+            hi = add_mismatch(hi, uint32_t(m >> 32), mine);
         }
     }
-    return peers;
+    return ~(uint64_t(hi) << 32 | lo);
 }
 
 // Whether every item of the wavefront where ok holds has the same digit (a
@@ -736,24 +738,21 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_write(
 
 // ---------------------------------------------------------------------------
 // Small batches (at most kSmallPairs pairs): the whole cast in one workgroup
-// of kSmallThreads threads, keys and values in LDS. Same stable LSD passes
-// (the pairs are spread evenly over the wavefronts in whole trips of 64:
-// wave w owns positions [w*span, (w+1)*span), walked 64 at a time; equal
-// digits ranked with ballots and one LDS atomic per digit group)
-// and the same segment build, without the kernel chain: for a few thousand
-// pairs the multi-kernel cast is all launch and memory latency.
+// of kSmallThreads threads, without the kernel chain: for a few thousand pairs
+// the multi-kernel cast is all launch and memory latency. Same stable LSD
+// passes and segment build, the pairs in registers and LDS: they are spread
+// evenly over the wavefronts in whole trips of 64, wave w owning positions
+// [w*span, (w+1)*span), walked 64 at a time. All of it is one CU's issue rate,
+// so what counts is instructions per pair: bags come from one prefix sum over
+// marks at the bags' first pairs (not a walk over the bags), ranks from four
+// instructions a digit bit and one LDS read and add, a digit's counts of two
+// digits per word, and prefixes from DPP adds. Measured: SMALLFIG.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;  // 16
 constexpr int kSmallItems = 8;
-constexpr int kSmallSpan = kWave * kSmallItems;     // 512
-constexpr int kSmallPairs = kSmallWaves * kSmallSpan;  // 8192
-// Digits of up to 9 bits in the one-workgroup cast: its per-wave digit
-// counts stay in LDS (16 x 512), and 17- or 18-bit keys take two passes
-// instead of three.
-constexpr int kSmallRadixBits = 9;
-constexpr int kSmallRadix = 1 << kSmallRadixBits;
-static_assert(kSmallRadix <= kSmallThreads, "one digit per thread in the digit scan");
-static_assert(kSmallPairs == kSmallItems * kSmallThreads, "k_cast_small stages one item per trip");
+constexpr int kSmallPairs = kSmallThreads * kSmallItems;  // 8192
+constexpr int kSmallWords = 1 << (kMaxRadixBits - 1);  // of two digits' counts per wave
+static_assert(kSmallWords <= kSmallThreads, "one word per thread in the digit scan");
 
 // With FL > 0 (tc_embed_forward_cast) the workgroups after the first run the
 // forward gather-reduce beside it, FL lanes per bag: a small cast keeps one
@@ -765,11 +764,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_cast_small(
     int32_t bags_per_table, int32_t n, int bits, bool positions, int32_t *__restrict__ unique_rows,
     int32_t *__restrict__ seg_offsets, int32_t *__restrict__ casted_src,
     int32_t *__restrict__ casted_dst, int32_t *__restrict__ num_unique, FwdSlice fs) {
-    // keys ping-pong between two buffers; values have one: every item of a
-    // pass is in registers before the pass writes any (barriers between)
-    __shared__ int32_t keys[2][kSmallPairs];
+    // every item of a pass is in registers before the pass writes any
+    // (barriers between), so one buffer each does
+    __shared__ int32_t keys[kSmallPairs];
     __shared__ int32_t vals[kSmallPairs];
-    __shared__ int32_t wcount[kSmallWaves][kSmallRadix];
+    __shared__ uint32_t wcount[kSmallWaves][kSmallWords];
+    __shared__ int32_t wsum[kSmallWaves];
     if constexpr (FL > 0) {
         if (blockIdx.x > 0) {  // uniform: a forward workgroup
             constexpr int64_t kWaves = kSmallThreads / kWave;
@@ -778,150 +778,184 @@ __global__ __launch_bounds__(kSmallThreads) void k_cast_small(
             return;
         }
     }
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-
-    // (src, dst) pairs from the bag-major CSR index: 16 lanes per bag. The
-    // index, the bag offsets and the table offsets are first staged in LDS
-    // (in the value buffer, the second key buffer and the digit counters)
-    // with independent loads, so the walk over bags waits for memory once.
-    // The index shares the value buffer: position j's index is read and its
-    // value then written by the same thread, and no other.
-    {
-        constexpr int kLanes = 16;
-        const int sub = tid & (kLanes - 1);
-        const bool staged = num_bags < kSmallPairs && num_tables <= kSmallWaves * kSmallRadix;
-        int32_t *s_idx = vals, *s_bo = keys[1], *s_off = &wcount[0][0];
-        if (staged) {
-            // every load issued before the first LDS store (n and num_bags
-            // + 1 are at most kSmallPairs = kSmallItems * kSmallThreads), so
-            // the staging waits for memory once, not once per trip
-            int32_t vi[kSmallItems], vb[kSmallItems];
-#pragma unroll
-            for (int i = 0; i < kSmallItems; ++i) {
-                const int32_t j = tid + i * kSmallThreads;
-                vi[i] = j < n ? indices[j] : 0;
-                vb[i] = j <= num_bags ? bag_offsets[j] : 0;
-            }
-            for (int32_t t = tid; t < num_tables; t += kSmallThreads)
-                s_off[t] = int32_t(table_row_offset[t]);
-#pragma unroll
-            for (int i = 0; i < kSmallItems; ++i) {
-                const int32_t j = tid + i * kSmallThreads;
-                if (j < n) s_idx[j] = vi[i];
-                if (j <= num_bags) s_bo[j] = vb[i];
-            }
-            __syncthreads();
-        }
-        for (int32_t g = tid / kLanes; g < num_bags; g += kSmallThreads / kLanes) {
-            const int32_t beg = staged ? s_bo[g] : bag_offsets[g];
-            const int32_t end = staged ? s_bo[g + 1] : bag_offsets[g + 1];
-            const int32_t t = g / bags_per_table;
-            const int32_t base = staged ? s_off[t] : int32_t(table_row_offset[t]);
-            for (int32_t j = beg + sub; j < end; j += kLanes) {
-                keys[0][j] = base + (staged ? s_idx[j] : indices[j]);
-                vals[j] = positions ? j : g;
-            }
-        }
-    }
-    __syncthreads();
-
-    const int passes = (bits + kSmallRadixBits - 1) / kSmallRadixBits;
-    const int per_pass = (bits + passes - 1) / passes;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
     // trips of 64 positions per wavefront (at most kSmallItems), so that
     // every wavefront holds a share of the pairs
     const int trips = (n + kSmallThreads - 1) / kSmallThreads;
-    const int32_t base = w * trips * kWave;
-    int cur = 0;
+    const int32_t base = w * trips * kWave + lane;
+    int32_t key[kSmallItems], val[kSmallItems];
+
+    // (src, dst) pairs from the bag-major CSR index. All loads that can be
+    // are issued together; marks[j] then counts the bags that start at pair j,
+    // and the sum of the marks up to j, less one, is j's bag (the last one
+    // starting at or before it).
+    {
+        int32_t *marks = vals, *row_off = reinterpret_cast<int32_t *>(&wcount[0][0]);
+        constexpr int kOffs = kSmallWaves * kSmallWords;
+        int32_t start[kSmallItems];
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            const int32_t j = base + i * kWave, g = tid + i * kSmallThreads;
+            key[i] = i < trips ? indices[min(j, n - 1)] : 0;
+            start[i] = g < num_bags ? bag_offsets[g] : n;
+        }
+        for (int32_t t = tid; t < num_tables && t < kOffs; t += kSmallThreads)
+            row_off[t] = int32_t(table_row_offset[t]);
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) marks[tid + i * kSmallThreads] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i)
+            if (start[i] < n) atomicAdd(&marks[start[i]], 1);
+        for (int32_t g = tid + kSmallPairs; g < num_bags; g += kSmallThreads) {
+            const int32_t b = bag_offsets[g];  // bags without pairs beyond the first 8192
+            if (b < n) atomicAdd(&marks[b], 1);
+        }
+        __syncthreads();
+        int32_t run = 0;
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            if (i >= trips) continue;  // uniform
+            const int32_t j = base + i * kWave;
+            val[i] = wave_prefix(j < n ? marks[j] : 0) + run;
+            run = __builtin_amdgcn_readlane(val[i], kWave - 1);
+        }
+        if (lane == 0) wsum[w] = run;
+        __syncthreads();
+        int32_t before = -1;
+#pragma unroll
+        for (int ww = 0; ww < kSmallWaves; ++ww)
+            if (ww < w) before += wsum[ww];
+        const float inv = 1.0f / float(bags_per_table);
+        const bool small_ids = num_bags < (1 << 22);  // exact in fp32
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            if (i >= trips) continue;  // uniform
+            const int32_t g = val[i] + before;
+            int32_t t;
+            if (small_ids) {  // the quotient is off by one at most
+                t = int32_t(float(g) * inv);
+                const int32_t r = g - t * bags_per_table;
+                t += (r >= bags_per_table) - (r < 0);
+            } else {
+                t = g / bags_per_table;
+            }
+            key[i] += num_tables <= kOffs ? row_off[t] : int32_t(table_row_offset[t]);
+            val[i] = positions ? base + i * kWave : g;
+        }
+        __syncthreads();  // the marks and row offsets have been read
+    }
+
+    const int passes = (bits + kMaxRadixBits - 1) / kMaxRadixBits;
+    const int per_pass = (bits + passes - 1) / passes;
     for (int p = 0; p < passes; ++p) {
         const int shift = p * per_pass;
         const int pbits = shift + per_pass <= bits ? per_pass : bits - shift;
         const uint32_t mask = (1u << pbits) - 1u;
-        for (int i = tid; i < kSmallWaves * kSmallRadix; i += kSmallThreads)
-            (&wcount[0][0])[i] = 0;
-        __syncthreads();
-        int32_t key[kSmallItems], val[kSmallItems], lower_n[kSmallItems], leader[kSmallItems],
-            old[kSmallItems];
+        const int words = 1 << (pbits - 1);  // pbits >= 1
+        for (int i = tid; i < kSmallWaves << (pbits - 1); i += kSmallThreads)
+            wcount[i >> (pbits - 1)][i & (words - 1)] = 0;
+        if (p > 0) {
 #pragma unroll
-        for (int i = 0; i < kSmallItems; ++i) {
-            old[i] = lower_n[i] = 0;
-            leader[i] = lane;
-            key[i] = val[i] = 0;
-            if (i >= trips) continue;  // uniform
-            const int32_t j = base + i * kWave + lane;
-            const bool ok = j < n;
-            key[i] = ok ? keys[cur][j] : 0;
-            val[i] = ok ? vals[j] : 0;
-            const uint32_t d = (uint32_t(key[i]) >> shift) & mask;
-            uint64_t act;
-            const uint64_t peers =
-                all_same_digit(d, ok, &act) ? act : match_digit_n<kSmallRadixBits>(d, ok, pbits);
-            const uint64_t lower = peers & lanemask_lt(lane);
-            lower_n[i] = __popcll(lower);
-            leader[i] = peers ? __builtin_ctzll(peers) : lane;
-            old[i] = 0;
-            if (ok && lower == 0) old[i] = atomicAdd(&wcount[w][d], __popcll(peers));
+            for (int i = 0; i < kSmallItems; ++i)
+                if (i < trips) {
+                    const int32_t j = min(base + i * kWave, n - 1);
+                    key[i] = keys[j];
+                    val[i] = vals[j];
+                }
         }
+        __syncthreads();
+        // every lane reads its digit's count before the lowest peer adds the
+        // item's to it: a wave's LDS operations complete in order
         int32_t rank[kSmallItems];
 #pragma unroll
-        for (int i = 0; i < kSmallItems; ++i)
-            rank[i] = i < trips ? __shfl(old[i], leader[i], kWave) + lower_n[i] : 0;
+        for (int i = 0; i < kSmallItems; ++i) {
+            if (i >= trips) continue;  // uniform
+            const bool ok = base + i * kWave < n;
+            const uint32_t d = (uint32_t(key[i]) >> shift) & mask;
+            const uint64_t peers = match_digit_n(d, ok, pbits);
+            const int32_t below = count_below(peers);
+            const int sh = 16 * (d & 1);
+            uint32_t *count = &wcount[w][d >> 1];
+            rank[i] = int32_t(__hip_atomic_load(count, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WAVEFRONT) >> sh & 0xffff) +
+                      below;
+            if (ok && below == 0) atomicAdd(count, uint32_t(__popcll(peers)) << sh);
+        }
         __syncthreads();
         {
-            // digit d = tid (threads past the radix hold zeros): start of each
-            // wave's run, in digit order then wave order
-            int32_t c[kSmallWaves], my = 0;
+            // digits 2 tid and 2 tid + 1: start of each wave's run, in digit
+            // order then wave order
+            uint32_t c[kSmallWaves];
+            int32_t n0 = 0, n1 = 0;
 #pragma unroll
             for (int ww = 0; ww < kSmallWaves; ++ww) {
-                c[ww] = tid < kSmallRadix ? wcount[ww][tid] : 0;
-                my += c[ww];
+                c[ww] = tid < words ? wcount[ww][tid] : 0;
+                n0 += c[ww] & 0xffff, n1 += c[ww] >> 16;
             }
             int32_t tot;
-            int32_t r = block_scan<kSmallThreads>(my, &tot);
-            if (tid < kSmallRadix) {
+            int32_t r0 = block_scan<kSmallThreads>(n0 + n1, &tot), r1 = r0 + n0;
+            if (tid < words) {
 #pragma unroll
                 for (int ww = 0; ww < kSmallWaves; ++ww) {
-                    wcount[ww][tid] = r;
-                    r += c[ww];
+                    wcount[ww][tid] = uint32_t(r0) | uint32_t(r1) << 16;
+                    r0 += c[ww] & 0xffff, r1 += c[ww] >> 16;
                 }
             }
         }
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kSmallItems; ++i) {
-            if (i < trips && base + i * kWave + lane < n) {
+            if (i < trips && base + i * kWave < n) {
                 const uint32_t d = (uint32_t(key[i]) >> shift) & mask;
-                const int32_t lp = wcount[w][d] + rank[i];
-                keys[cur ^ 1][lp] = key[i];
+                const int32_t lp = int32_t(wcount[w][d >> 1] >> (16 * (d & 1)) & 0xffff) + rank[i];
+                keys[lp] = key[i];
                 vals[lp] = val[i];
             }
         }
         __syncthreads();
-        cur ^= 1;
     }
 
-    // segment build: thread tid owns sorted positions tid*trips .. tid*trips +
-    // trips - 1
-    int32_t head[kSmallItems], c = 0;
+    // segment build, on the sorted positions in the same trips
+    uint64_t heads[kSmallItems];
+    int32_t prev = base >= kWave ? keys[min(base - lane, n) - 1] : 0;  // the key before item i
+    int32_t count = 0;
 #pragma unroll
     for (int i = 0; i < kSmallItems; ++i) {
-        const int32_t j = tid * trips + i;
-        head[i] = i < trips && j < n && (j == 0 || keys[cur][j] != keys[cur][j - 1]);
-        c += head[i];
+        if (i >= trips) continue;  // uniform
+        const int32_t j = base + i * kWave;
+        key[i] = keys[min(j, n - 1)];
+        val[i] = vals[min(j, n - 1)];
+        // wave_shr:1, lane 0 taking the one before
+        const int32_t before = __builtin_amdgcn_update_dpp(prev, key[i], 0x138, 0xf, 0xf, false);
+        heads[i] = __ballot(j < n && (j == 0 || key[i] != before));
+        count += __popcll(heads[i]);
+        prev = __builtin_amdgcn_readlane(key[i], kWave - 1);
     }
-    int32_t total;
-    int32_t run = block_scan<kSmallThreads>(c, &total);
+    if (lane == 0) wsum[w] = count;
+    __syncthreads();
+    int32_t run = 0, total = 0;
+#pragma unroll
+    for (int ww = 0; ww < kSmallWaves; ++ww) {
+        if (ww < w) run += wsum[ww];
+        total += wsum[ww];
+    }
 #pragma unroll
     for (int i = 0; i < kSmallItems; ++i) {
-        const int32_t j = tid * trips + i;
-        if (i < trips && j < n) {
-            run += head[i];
-            casted_src[j] = vals[j];
-            if (casted_dst) casted_dst[j] = run - 1;
-            if (head[i]) {
-                unique_rows[run - 1] = keys[cur][j];
-                seg_offsets[run - 1] = j;
+        if (i >= trips) continue;  // uniform
+        const int32_t j = base + i * kWave;
+        if (j < n) {
+            const bool head = heads[i] >> lane & 1u;
+            const int32_t incl = run + count_below(heads[i]) + head;
+            casted_src[j] = val[i];
+            if (casted_dst) casted_dst[j] = incl - 1;
+            if (head) {
+                unique_rows[incl - 1] = key[i];
+                seg_offsets[incl - 1] = j;
             }
         }
+        run += __popcll(heads[i]);
     }
     if (tid == 0) {
         seg_offsets[total] = n;
