@@ -88,8 +88,16 @@ def _ptr(t: torch.Tensor | None, dtype=None, name="tensor"):
     return t.data_ptr()
 
 
+# The current stream's handle without the Stream object that
+# torch.cuda.current_stream() makes: 0.2 us against 2.8 us, in a call whose
+# launch takes 3.2 us (absent from a torch built without a GPU backend).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int | None:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
