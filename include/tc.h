@@ -160,11 +160,10 @@ tc_status tc_cast_index(const int64_t *table_row_offset, int32_t num_tables,
  * results bit for bit, the forward overlapped with the cast: casting needs
  * only the index array, so it can run while the forward gather-reduce reads
  * the table (the paper's runtime hides the casting latency inside forward
- * propagation, Sec. IV-B). For dim in [36, 256] the forward runs in the
- * cast's own launches: beside the single-workgroup cast of a small batch
- * (up to 8192 pairs), else in the launch that builds the cast's (row, bag)
- * pairs from the same index array; for other dims the forward runs first,
- * then the cast. Arguments are those of the two calls (max_table_rows
+ * propagation, Sec. IV-B). The forward runs in the cast's own launches: beside
+ * the single-workgroup cast of a small batch (up to 8192 pairs; with dim > 256
+ * before it), else in the launch that builds the cast's (row, bag) pairs from
+ * the same index array. Arguments are those of the two calls (max_table_rows
  * and the workspace as for tc_cast_index, W and out as for
  * tc_embed_forward); out must not overlap the cast's outputs or workspace.
  * Every argument is checked before anything is launched.

@@ -52,7 +52,7 @@
 // does not matter); nothing here depends on scheduling order.
 //
 // tc_embed_forward_cast runs the forward gather-reduce in the cast's
-// launches: k_forward_build (pairs built per tile, then workgroups of the
+// launches: k_forward_build (workgroups building pairs, then workgroups of the
 // forward) or, for a small batch, beside the one k_cast_small workgroup.
 #include "tc_group_sum.h"
 
@@ -72,8 +72,6 @@ constexpr int kWaveSpan = kWave * kItems;             // 512
 constexpr int kSortTile = kSortWaves * kWaveSpan;     // 4096
 // Full groups of this many tiles of a segment have their digit counts summed.
 constexpr int kGroupTiles = 16;
-// Tiles of the pair build, of kBlock threads.
-constexpr int kTile = kBlock * kItems;                // 2048
 // Table-local sorting for at most this many tables (one thread per table
 // lays the segments out).
 constexpr int kMaxSegTables = kBlock;
@@ -164,10 +162,6 @@ __device__ TileRec tile_record(const SegLayout &L, int32_t num_tables, int32_t t
     return r;
 }
 
-// Bag offsets staged per tile by build_tile (a 2048-pair tile spans at most
-// 2048 bags with pairs; more only with bags without pairs between them).
-constexpr int kStageBags = 2048;
-
 // The records of all num_tile_slots tile slots, written by one workgroup.
 __device__ void write_tile_records(const int32_t *__restrict__ bag_offsets,
                                    const int64_t *__restrict__ table_row_offset,
@@ -202,86 +196,23 @@ __device__ __forceinline__ void prepare_sort(const SortPrep &sp, int64_t b, int6
                            sp.recs, sp.tile_slots);
 }
 
-// The (src, dst) pairs [b*kTile, (b+1)*kTile): keys are table-local rows when
-// `local`, else global rows; values are bag ids (dst). Pair j's bag comes from
-// a search: the bag holding the tile's first pair by a 64-way search of the
-// bag offsets, then each pair's by binary search of the tile's bag offsets
-// staged in LDS.
-__device__ void build_tile(int32_t b, const int32_t *__restrict__ indices,
-                           const int32_t *__restrict__ bag_offsets,
-                           const int64_t *__restrict__ table_row_offset, int64_t num_bags,
-                           int32_t bags_per_table, int32_t n, bool local,
-                           int32_t *__restrict__ keys, int32_t *__restrict__ vals) {
-    __shared__ int32_t sbo[kStageBags + 1];
-    __shared__ int32_t s_g0;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    const int32_t p0 = b * kTile;
-    const int32_t p1 = n - p0 < kTile ? n : p0 + kTile;
-    if (w == 0) {
-        // the last bag g with bag_offsets[g] <= p0, the range narrowed
-        // 64-fold per step
-        int64_t lo = 0, hi = num_bags;
-        while (hi - lo > 1) {
-            const int64_t step = (hi - lo + kWave - 1) / kWave;
-            const int64_t g = lo + lane * step;
-            const bool le = g < hi && bag_offsets[g] <= p0;
-            const uint64_t m = __ballot(le);
-            const int l = m ? 63 - __builtin_clzll(m) : 0;
-            lo = lo + l * step;
-            hi = lo + step < hi ? lo + step : hi;
-        }
-        if (lane == 0) s_g0 = int32_t(lo);
-    }
-    __syncthreads();
-    const int64_t g0 = s_g0;
-    const int32_t nst = int32_t(num_bags - g0 < kStageBags ? num_bags - g0 : kStageBags);
-    for (int32_t i = tid; i <= nst; i += kBlock) sbo[i] = bag_offsets[g0 + i];
-    __syncthreads();
-    // whether the staged offsets hold the bag of every pair of the tile
-    const bool staged = g0 + nst == num_bags || sbo[nst] >= p1;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int32_t j = p0 + i * kBlock + tid;
-        if (j < p1) {
-            int64_t g;
-            if (staged) {
-                int32_t lo = 0, hi = nst - 1;
-                while (lo < hi) {
-                    const int32_t mid = (lo + hi + 1) / 2;
-                    if (sbo[mid] <= j) lo = mid; else hi = mid - 1;
-                }
-                g = g0 + lo;
-            } else {
-                int64_t lo = g0, hi = num_bags - 1;
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi + 1) / 2;
-                    if (bag_offsets[mid] <= j) lo = mid; else hi = mid - 1;
-                }
-                g = lo;
-            }
-            const int32_t idx = indices[j];
-            keys[j] = local ? idx : int32_t(table_row_offset[g / bags_per_table] + idx);
-            vals[j] = int32_t(g);
-        }
-    }
-}
-
-// (src, dst) pairs by a walk over the bags (tc_cast_index, tc_argsort_rows):
-// one group of 16 lanes per bag writes that bag's pairs; keys as in
-// build_tile, values bag ids, or pair positions when `positions` (an argsort).
-// On its own this walk takes less time than build_tile's searches.
-__global__ __launch_bounds__(kBlock) void k_build_keys(
-    const int32_t *__restrict__ indices, const int32_t *__restrict__ bag_offsets,
-    const int64_t *__restrict__ table_row_offset, int64_t num_bags, int32_t bags_per_table,
-    int32_t num_tables, bool local, bool positions, SortPrep sp, int32_t *__restrict__ keys,
-    int32_t *__restrict__ vals) {
-    prepare_sort(sp, blockIdx.x, gridDim.x, bag_offsets, table_row_offset, num_bags,
-                 bags_per_table, num_tables);
-    constexpr int kLanes = 16;
-    const int64_t group = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kLanes;
-    const int64_t ngroups = (int64_t(gridDim.x) * blockDim.x) / kLanes;
+// (src, dst) pairs by a walk over the bags, and the share of workgroup `b` of
+// `blocks` in prepare_sort: one group of 16 lanes per bag writes that bag's
+// pairs. Keys are table-local rows when `local`, else global rows; values are
+// bag ids (dst), or pair positions when `positions` (an argsort).
+__device__ __forceinline__ void build_pairs(int64_t b, int64_t blocks,
+                                            const int32_t *__restrict__ indices,
+                                            const int32_t *__restrict__ bag_offsets,
+                                            const int64_t *__restrict__ table_row_offset,
+                                            int64_t num_bags, int32_t bags_per_table,
+                                            int32_t num_tables, bool local, bool positions,
+                                            const SortPrep &sp, int32_t *__restrict__ keys,
+                                            int32_t *__restrict__ vals) {
+    prepare_sort(sp, b, blocks, bag_offsets, table_row_offset, num_bags, bags_per_table,
+                 num_tables);
+    constexpr int kLanes = 16, kGroups = kBlock / kLanes;
     const int sub = threadIdx.x & (kLanes - 1);
-    for (int64_t g = group; g < num_bags; g += ngroups) {
+    for (int64_t g = b * kGroups + threadIdx.x / kLanes; g < num_bags; g += blocks * kGroups) {
         const int32_t beg = bag_offsets[g], end = bag_offsets[g + 1];
         const int64_t base = local ? 0 : table_row_offset[g / bags_per_table];
         for (int32_t j = beg + sub; j < end; j += kLanes) {
@@ -290,27 +221,38 @@ __global__ __launch_bounds__(kBlock) void k_build_keys(
         }
     }
 }
+// Workgroups for it.
+inline unsigned build_grid(int64_t num_bags) {
+    return grid_for(num_bags, kBlock / 16, int64_t(device_cus()) * 8);
+}
 
-// The pair build (build_tile, one tile per workgroup) with the forward
-// gather-reduce in one launch (tc_embed_forward_cast): the first `tiles`
-// workgroups build the tiles, the others run the forward (FL lanes per bag,
-// as k_forward). Both read the index array; the tile workgroups' searches and
+// The pair build alone (tc_cast_index, tc_argsort_rows).
+__global__ __launch_bounds__(kBlock) void k_build_keys(
+    const int32_t *__restrict__ indices, const int32_t *__restrict__ bag_offsets,
+    const int64_t *__restrict__ table_row_offset, int64_t num_bags, int32_t bags_per_table,
+    int32_t num_tables, bool local, bool positions, SortPrep sp, int32_t *__restrict__ keys,
+    int32_t *__restrict__ vals) {
+    build_pairs(blockIdx.x, gridDim.x, indices, bag_offsets, table_row_offset, num_bags,
+                bags_per_table, num_tables, local, positions, sp, keys, vals);
+}
+
+// The pair build with the forward gather-reduce in one launch
+// (tc_embed_forward_cast): the first `builders` workgroups build pairs, the
+// others run the forward (as k_forward). Both read the index array; the pairs'
 // stores stay out of the forward's chains of dependent loads, and their
 // latency hides behind the forward's.
-template <int FL>
+template <int LANES, int CHUNKS>
 __global__ __launch_bounds__(kBlock) void k_forward_build(
-    FwdSlice f, int32_t num_tables, int32_t n, bool local, SortPrep sp, int32_t tiles,
+    FwdSlice f, int32_t num_tables, bool local, SortPrep sp, int32_t builders,
     int32_t *__restrict__ keys, int32_t *__restrict__ vals) {
-    if (int32_t(blockIdx.x) < tiles) {  // uniform
-        prepare_sort(sp, blockIdx.x, tiles, f.offsets, f.table_row_offset, f.bag_hi,
-                     f.bags_per_table, num_tables);
-        build_tile(blockIdx.x, f.ids, f.offsets, f.table_row_offset, f.bag_hi, f.bags_per_table,
-                   n, local, keys, vals);
+    if (int32_t(blockIdx.x) < builders) {  // uniform
+        build_pairs(blockIdx.x, builders, f.ids, f.offsets, f.table_row_offset, f.bag_hi,
+                    f.bags_per_table, num_tables, local, false, sp, keys, vals);
         return;
     }
     constexpr int64_t kWaves = kBlock / kWave;
-    forward_bags<FL, 1>(f, (int64_t(blockIdx.x) - tiles) * kWaves + threadIdx.x / kWave,
-                        (int64_t(gridDim.x) - tiles) * kWaves);
+    forward_bags<LANES, CHUNKS>(f, (int64_t(blockIdx.x) - builders) * kWaves + threadIdx.x / kWave,
+                                (int64_t(gridDim.x) - builders) * kWaves);
 }
 
 // The tile of this workgroup of a pass: consecutive tiles on one XCD
@@ -1015,18 +957,17 @@ inline int32_t seg_capacity(int32_t num_tables) {
 
 struct CastPlan {
     int64_t sort_tiles;  // tile slots of a radix pass (all segments)
-    int64_t build_tiles, seg_tiles;  // of the pair build (kTile), the segment build (kSortTile)
+    int64_t seg_tiles;   // tiles of the segment build (plain tiles of kSortTile)
     size_t off_ka, off_va, off_kb, off_vb, off_counts, counts_bytes, off_heads, off_recs, bytes;
 };
 
 inline CastPlan cast_plan(int64_t n, int32_t num_tables) {
     CastPlan p{};
     const int32_t nseg = seg_capacity(num_tables);
-    p.build_tiles = (n + kTile - 1) / kTile;
     p.seg_tiles = (n + kSortTile - 1) / kSortTile;
     p.sort_tiles = p.seg_tiles + nseg;  // each segment adds at most one short tile
     const size_t arr = align_up(size_t(n) * 4);
-    const int64_t slots = p.build_tiles + nseg;
+    const int64_t slots = (n + 2047) / 2048 + nseg;  // a KB of counts each
     size_t o = 0;
     p.off_ka = o; o += arr;
     p.off_va = o; o += arr;
@@ -1036,7 +977,7 @@ inline CastPlan cast_plan(int64_t n, int32_t num_tables) {
     // for them (sort_digits)
     p.counts_bytes = align_up(size_t(slots) * 1024) + 1024;
     p.off_counts = o; o += p.counts_bytes;
-    p.off_heads = o; o += align_up(size_t(p.build_tiles) * 4);
+    p.off_heads = o; o += align_up(size_t(slots - nseg) * 4);
     p.off_recs = o; o += align_up(size_t(slots) * sizeof(TileRec));
     p.bytes = o;
     return p;
@@ -1099,8 +1040,8 @@ tc_status forward_alone(const FwdSlice &fwd, hipStream_t stream) {
 // tc_argsort_rows (values = pair positions). `what` names the entry point in
 // error messages. With fwd (tc_embed_forward_cast; values = bag ids), the
 // forward gather-reduce of all fwd->bag_hi bags runs too: beside the
-// single-workgroup cast, or as the key-building kernel of the radix sort,
-// or, for row shapes without such kernels, as its own kernel first.
+// single-workgroup cast (or, for rows of several chunks a lane, before it), or
+// in the key-building kernel of the radix sort.
 tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_offset,
                     int32_t num_tables, int32_t bags_per_table, int64_t total_rows,
                     int64_t max_table_rows, const int32_t *indices, const int32_t *bag_offsets,
@@ -1135,15 +1076,18 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     TC_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) == 0, TC_ERR_WORKSPACE,
                "%s: workspace must be 256-byte aligned", what);
 
-    const int fl = fwd ? ride_along_lanes(fwd->dim) : 0;
-    if (fwd && fl == 0) {
-        const tc_status st = forward_alone(*fwd, stream);
-        if (st != TC_OK) return st;
-    }
+    const RowShape shape = row_shape(fwd ? int(fwd->dim) : 4);
     if (num_pairs <= kSmallPairs) {
         // one workgroup in LDS (the workspace is not touched); the forward's
         // workgroups, if any, run beside it (one per CU at most: each holds
         // the kernel's LDS), one bag per lane group
+        // (rows of several chunks a lane have the forward first, as its own
+        // kernel: it needs more registers than 1024 threads have)
+        const int fl = fwd && shape.chunks == 1 ? shape.lanes : 0;
+        if (fwd && fl == 0) {
+            const tc_status st = forward_alone(*fwd, stream);
+            if (st != TC_OK) return st;
+        }
         unsigned fb = 0;
         if (fl) {
             const int64_t per_block = int64_t(kSmallThreads / kWave) * (kWave / fl);
@@ -1155,7 +1099,11 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
         indices, bag_offsets, table_row_offset, num_tables, int32_t(num_bags), bags_per_table, \
         int32_t(num_pairs), key_bits(total_rows), positions, unique_rows, seg_offsets,        \
         casted_src, casted_dst, num_unique, fs)
-        if (fl == 16) TC_SMALL(16);
+        if (fl == 1) TC_SMALL(1);
+        else if (fl == 2) TC_SMALL(2);
+        else if (fl == 4) TC_SMALL(4);
+        else if (fl == 8) TC_SMALL(8);
+        else if (fl == 16) TC_SMALL(16);
         else if (fl == 32) TC_SMALL(32);
         else if (fl == 64) TC_SMALL(64);
         else TC_SMALL(0);
@@ -1178,31 +1126,38 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     TileRec *recs = local ? reinterpret_cast<TileRec *>(ws + plan.off_recs) : nullptr;
     const int32_t sort_tiles = int32_t(plan.sort_tiles);
     const int32_t seg_tiles = int32_t(plan.seg_tiles);
-    const int32_t build_tiles = int32_t(plan.build_tiles);
 
     const SortDigits digits = sort_digits(plan, num_pairs, bits);
     const int passes = digits.passes, per_pass = digits.per_pass;
     int32_t *groups = reinterpret_cast<int32_t *>(ws + plan.off_counts + digits.counts_bytes);
     const SortPrep prep{recs, sort_tiles, groups, int64_t(digits.group_words) * passes};
-    if (fl) {
-        // the tiles' pair builds, then the forward's workgroups, in one launch
-        const int64_t per_block = int64_t(kBlock / kWave) * (kWave / fl);
+    if (fwd) {
+        // the pair build's workgroups, then the forward's, in one launch
+        const int64_t per_block = int64_t(kBlock / kWave) * (kWave / shape.lanes);
+        const unsigned builders = build_grid(num_bags);
         const unsigned grid =
-            unsigned(build_tiles) + grid_for(num_bags, per_block, int64_t(device_cus()) * 32);
-#define TC_FWD_BUILD(FL)                                                                     \
-    k_forward_build<FL><<<grid, kBlock, 0, stream>>>(*fwd, num_tables, int32_t(num_pairs),    \
-                                                     local, prep, build_tiles, ka, va)
-        if (fl == 16) TC_FWD_BUILD(16);
-        else if (fl == 32) TC_FWD_BUILD(32);
-        else TC_FWD_BUILD(64);
+            builders + grid_for(num_bags, per_block, int64_t(device_cus()) * 32);
+#define TC_FWD_BUILD(L, C)                                                                   \
+    if (shape.lanes == L && shape.chunks == C)                                               \
+        k_forward_build<L, C><<<grid, kBlock, 0, stream>>>(*fwd, num_tables, local, prep,     \
+                                                           int32_t(builders), ka, va);
+        TC_FWD_BUILD(1, 1)
+        TC_FWD_BUILD(2, 1)
+        TC_FWD_BUILD(4, 1)
+        TC_FWD_BUILD(8, 1)
+        TC_FWD_BUILD(16, 1)
+        TC_FWD_BUILD(32, 1)
+        TC_FWD_BUILD(64, 1)
+        TC_FWD_BUILD(64, 2)
+        TC_FWD_BUILD(64, 3)
+        TC_FWD_BUILD(64, 4)
 #undef TC_FWD_BUILD
         tc_status st = check_launch("k_forward_build");
         if (st != TC_OK) return st;
     } else {
-        const unsigned grid = grid_for(num_bags, kBlock / 16, int64_t(device_cus()) * 8);
-        k_build_keys<<<grid, kBlock, 0, stream>>>(indices, bag_offsets, table_row_offset,
-                                                  num_bags, bags_per_table, num_tables, local,
-                                                  positions, prep, ka, va);
+        k_build_keys<<<build_grid(num_bags), kBlock, 0, stream>>>(
+            indices, bag_offsets, table_row_offset, num_bags, bags_per_table, num_tables, local,
+            positions, prep, ka, va);
         tc_status st = check_launch("k_build_keys");
         if (st != TC_OK) return st;
     }

@@ -100,14 +100,6 @@ __device__ __forceinline__ void forward_bags(const FwdSlice &f, int64_t wave, in
     }
 }
 
-// Lanes per bag of a forward run inside the cast's kernels: the lane groups
-// of one float4 chunk per lane and at least 16 lanes (dim 36..256); 0 for
-// other row shapes (the forward then runs as its own kernel).
-inline int ride_along_lanes(int32_t dim) {
-    const RowShape s = row_shape(dim);
-    return s.chunks == 1 && s.lanes >= 16 ? s.lanes : 0;
-}
-
 // The forward over all num_bags bags as its own kernel (tc_gather_reduce.hip).
 tc_status launch_forward(const float *W, int32_t dim, const int32_t *ids, const int32_t *offsets,
                          const int64_t *table_row_offset, int32_t bags_per_table,
