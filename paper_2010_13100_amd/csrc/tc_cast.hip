@@ -17,9 +17,10 @@
 //     A pass reads and writes 8 bytes per pair plus a 4-byte read for the
 //     histogram. The last pass writes the values straight into casted_src.
 //  3. Segment build (the scan and cumulative sum of Algorithm 2):
-//       k_seg_count  heads (key differs from its predecessor) per tile
-//       k_seg_write  casted_dst, unique_rows, seg_offsets, *num_unique (each
-//                    block sums the head counts of the tiles before it)
+//       k_segments   counts the heads (key differs from its predecessor) per
+//                    tile, then casted_dst, unique_rows, seg_offsets and
+//                    *num_unique from the counts of the tiles before; for
+//                    large batches in two launches, k_seg_count, k_seg_write
 //
 // What bounds it at a batch of a million pairs is not bandwidth (a pass moves
 // 20 bytes per pair, 4 us) but the number of launches and, in each, a chain of
@@ -49,7 +50,8 @@
 // walks them 64 at a time, lane l taking position base + 64*i + l, so tile
 // order = (wave, iteration, lane) order and every pass is stable. The only
 // atomics on global memory are the group sums' (whole numbers, whose order
-// does not matter); nothing here depends on scheduling order.
+// does not matter) and the segment build's; no result depends on scheduling
+// order.
 //
 // tc_embed_forward_cast runs the forward gather-reduce in the cast's
 // launches: k_forward_build (workgroups building pairs, then workgroups of the
@@ -175,12 +177,14 @@ __device__ void write_tile_records(const int32_t *__restrict__ bag_offsets,
 }
 
 // Where the sort's bookkeeping is, for the kernels before its first pass:
-// tile records to write (null: none) and group sums to clear.
+// tile records to write (null: none), and words to clear.
 struct SortPrep {
     TileRec *recs;
     int32_t tile_slots;
     int32_t *groups;
     int64_t group_words;
+    int32_t *state;  // of the segment build, cleared too
+    int64_t state_words;
 };
 // The share of workgroup `b` of `blocks` in that; workgroup 0 also writes the
 // records.
@@ -191,6 +195,8 @@ __device__ __forceinline__ void prepare_sort(const SortPrep &sp, int64_t b, int6
                                              int32_t num_tables) {
     for (int64_t i = b * kBlock + threadIdx.x; i < sp.group_words; i += blocks * kBlock)
         sp.groups[i] = 0;
+    for (int64_t i = b * kBlock + threadIdx.x; i < sp.state_words; i += blocks * kBlock)
+        sp.state[i] = 0;
     if (sp.recs && b == 0)
         write_tile_records(bag_offsets, table_row_offset, num_bags, bags_per_table, num_tables,
                            sp.recs, sp.tile_slots);
@@ -614,7 +620,85 @@ __device__ __forceinline__ Heads segment_heads(const int32_t *__restrict__ keys,
     return h;
 }
 
-// 3a. number of segment heads per tile.
+// casted_dst, unique_rows and seg_offsets of one wavefront's span, `run` heads
+// coming before it.
+__device__ __forceinline__ void write_segments(const Heads &h, int64_t base, int64_t n,
+                                               int32_t run, int32_t *__restrict__ unique_rows,
+                                               int32_t *__restrict__ seg_offsets,
+                                               int32_t *__restrict__ casted_dst) {
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int64_t j = base + i * kWave + lane;
+        const bool head = h.lanes[i] >> lane & 1u;
+        const int32_t incl = run + count_below(h.lanes[i]) + head;
+        if (j < n) {
+            if (casted_dst) casted_dst[j] = incl - 1;
+            if (head) {
+                unique_rows[incl - 1] = h.key[i];
+                seg_offsets[incl - 1] = int32_t(j);
+            }
+            if (j == n - 1) seg_offsets[incl] = int32_t(n);
+        }
+        run += __popcll(h.lanes[i]);
+    }
+}
+
+// 3a. casted_dst (inclusive head count - 1), unique_rows and seg_offsets in one
+// launch, up to kOneLaunchTiles tiles: a workgroup counts its tile's heads and
+// publishes the count, then adds up the counts of the tiles before it, waiting
+// for those still missing. Tiles are handed out in the order in which
+// workgroups start (state[0]), and each publishes before it waits, so whatever
+// a workgroup waits for comes from one that has started and waits for nothing
+// first: every wait ends, however many workgroups are resident. A count is one
+// word, state[1 + tile] = count + 1, zero until published (cleared by the pair
+// build), stored and loaded at agent scope, so nothing else needs ordering.
+// The workgroup of the last tile writes *num_unique.
+// The tickets cost 12 ns each, one after another, so two launches take less
+// time for many tiles. Measured (us of the kernels, against the two's): 35
+// tiles 5.0 and 6.6, 41 tiles 5.5 and 9.3, 160 tiles 7.4 and 9.1 (but the whole
+// step, where launches overlap, 61.8 and 60.8), 320 tiles 10.7 and 9.8, 1280
+// tiles 33.9 and 15.9.
+constexpr int kOneLaunchTiles = 96;
+__global__ __launch_bounds__(kSortThreads) void k_segments(
+    const int32_t *__restrict__ keys, int64_t n, int32_t tiles, int32_t *__restrict__ state,
+    int32_t *__restrict__ unique_rows, int32_t *__restrict__ seg_offsets,
+    int32_t *__restrict__ casted_dst, int32_t *__restrict__ num_unique) {
+    __shared__ int32_t wsum[kSortWaves];
+    __shared__ int32_t s_tile;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    if (tid == 0)
+        s_tile = __hip_atomic_fetch_add(&state[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int32_t b = __builtin_amdgcn_readfirstlane(s_tile);
+    const int64_t base = int64_t(b) * kSortTile + int64_t(w) * kWaveSpan;
+    const Heads h = segment_heads(keys, base, n);
+    if (lane == 0) wsum[w] = h.count;
+    __syncthreads();
+    int32_t run = 0, total = 0;
+#pragma unroll
+    for (int ww = 0; ww < kSortWaves; ++ww) {
+        if (ww < w) run += wsum[ww];
+        total += wsum[ww];
+    }
+    if (tid == 0)
+        __hip_atomic_store(&state[1 + b], total + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int32_t part = 0;
+    for (int32_t t = tid; t < b; t += kSortThreads) {
+        int32_t c;
+        while ((c = __hip_atomic_load(&state[1 + t], __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT)) == 0)
+            __builtin_amdgcn_s_sleep(1);
+        part += c - 1;
+    }
+    int32_t before;
+    block_scan<kSortThreads>(part, &before);
+    run += before;
+    if (b == tiles - 1 && tid == 0) *num_unique = before + total;
+    write_segments(h, base, n, run, unique_rows, seg_offsets, casted_dst);
+}
+
+// 3b. the same in two launches, for more tiles: number of heads per tile,
 __global__ __launch_bounds__(kSortThreads) void k_seg_count(const int32_t *__restrict__ keys,
                                                             int64_t n, int32_t tiles,
                                                             int32_t *__restrict__ tile_heads) {
@@ -633,10 +717,9 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_count(const int32_t *__res
     }
 }
 
-// 3b. casted_dst (inclusive head count - 1), unique_rows and seg_offsets.
-// Each block adds up the head counts of the tiles before it (a few loads per
-// thread even for thousands of tiles, so no separate scan kernel); the last
-// tile's writes *num_unique.
+// then the writes, where each workgroup adds up the head counts of the tiles
+// before it (a few loads per thread even for thousands of tiles, so no separate
+// scan kernel); the last tile's writes *num_unique.
 __global__ __launch_bounds__(kSortThreads) void k_seg_write(
     const int32_t *__restrict__ keys, int64_t n, int32_t tiles,
     const int32_t *__restrict__ tile_heads, int32_t *__restrict__ unique_rows,
@@ -661,21 +744,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_write(
         total += wsum[ww];
     }
     if (b == tiles - 1 && tid == 0) *num_unique = total;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int64_t j = base + i * kWave + lane;
-        const bool head = h.lanes[i] >> lane & 1u;
-        const int32_t incl = run + count_below(h.lanes[i]) + head;
-        if (j < n) {
-            if (casted_dst) casted_dst[j] = incl - 1;
-            if (head) {
-                unique_rows[incl - 1] = h.key[i];
-                seg_offsets[incl - 1] = int32_t(j);
-            }
-            if (j == n - 1) seg_offsets[incl] = int32_t(n);
-        }
-        run += __popcll(h.lanes[i]);
-    }
+    write_segments(h, base, n, run, unique_rows, seg_offsets, casted_dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -958,7 +1027,7 @@ inline int32_t seg_capacity(int32_t num_tables) {
 struct CastPlan {
     int64_t sort_tiles;  // tile slots of a radix pass (all segments)
     int64_t seg_tiles;   // tiles of the segment build (plain tiles of kSortTile)
-    size_t off_ka, off_va, off_kb, off_vb, off_counts, counts_bytes, off_heads, off_recs, bytes;
+    size_t off_ka, off_va, off_kb, off_vb, off_counts, counts_bytes, off_state, off_recs, bytes;
 };
 
 inline CastPlan cast_plan(int64_t n, int32_t num_tables) {
@@ -977,7 +1046,7 @@ inline CastPlan cast_plan(int64_t n, int32_t num_tables) {
     // for them (sort_digits)
     p.counts_bytes = align_up(size_t(slots) * 1024) + 1024;
     p.off_counts = o; o += p.counts_bytes;
-    p.off_heads = o; o += align_up(size_t(slots - nseg) * 4);
+    p.off_state = o; o += align_up(size_t(slots - nseg) * 4);
     p.off_recs = o; o += align_up(size_t(slots) * sizeof(TileRec));
     p.bytes = o;
     return p;
@@ -1122,7 +1191,7 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     int32_t *va = reinterpret_cast<int32_t *>(ws + plan.off_va);
     int32_t *kb = reinterpret_cast<int32_t *>(ws + plan.off_kb);
     int32_t *vb = reinterpret_cast<int32_t *>(ws + plan.off_vb);
-    int32_t *heads = reinterpret_cast<int32_t *>(ws + plan.off_heads);
+    int32_t *state = reinterpret_cast<int32_t *>(ws + plan.off_state);
     TileRec *recs = local ? reinterpret_cast<TileRec *>(ws + plan.off_recs) : nullptr;
     const int32_t sort_tiles = int32_t(plan.sort_tiles);
     const int32_t seg_tiles = int32_t(plan.seg_tiles);
@@ -1130,7 +1199,8 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     const SortDigits digits = sort_digits(plan, num_pairs, bits);
     const int passes = digits.passes, per_pass = digits.per_pass;
     int32_t *groups = reinterpret_cast<int32_t *>(ws + plan.off_counts + digits.counts_bytes);
-    const SortPrep prep{recs, sort_tiles, groups, int64_t(digits.group_words) * passes};
+    const SortPrep prep{recs,  sort_tiles,     groups, int64_t(digits.group_words) * passes,
+                        state, plan.seg_tiles <= kOneLaunchTiles ? plan.seg_tiles + 1 : 0};
     if (fwd) {
         // the pair build's workgroups, then the forward's, in one launch
         const int64_t per_block = int64_t(kBlock / kWave) * (kWave / shape.lanes);
@@ -1183,12 +1253,18 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     }
     const int32_t *sorted_keys = kin;
 
+    if (seg_tiles <= kOneLaunchTiles) {
+        k_segments<<<seg_tiles, kSortThreads, 0, stream>>>(sorted_keys, num_pairs, seg_tiles,
+                                                           state, unique_rows, seg_offsets,
+                                                           casted_dst, num_unique);
+        return check_launch("k_segments");
+    }
     k_seg_count<<<tile_grid(seg_tiles), kSortThreads, 0, stream>>>(sorted_keys, num_pairs,
-                                                                   seg_tiles, heads);
+                                                                   seg_tiles, state);
     tc_status st = check_launch("k_seg_count");
     if (st != TC_OK) return st;
     k_seg_write<<<tile_grid(seg_tiles), kSortThreads, 0, stream>>>(
-        sorted_keys, num_pairs, seg_tiles, heads, unique_rows, seg_offsets, casted_dst,
+        sorted_keys, num_pairs, seg_tiles, state, unique_rows, seg_offsets, casted_dst,
         num_unique);
     return check_launch("k_seg_write");
 }

@@ -28,6 +28,12 @@ def test_groups_of_tiles(tiles):
           seed=tiles)
 
 
+# the segment build in one launch (up to 96 tiles) and in two
+@pytest.mark.parametrize("pairs", [95 * TILE + 1, 96 * TILE, 96 * TILE + 1])
+def test_segment_build_launches(pairs):
+    check(f"{pairs} pairs", [300_000], [pairs], bags_per_table=1000, seed=pairs % 97)
+
+
 @pytest.mark.parametrize("tables,pairs", [(256, 40), (256, 700), (200, 4097), (37, 230)])
 def test_many_tables(tables, pairs):
     check(f"{tables} tables", [1000 + 13 * k for k in range(tables)],
