@@ -130,7 +130,9 @@ struct SplitWs {
     int64_t cap_pairs;  // 0: no workspace
     int32_t list_blocks;
     int32_t parts;
+    int32_t *turns;  // kXcds counters, kTurnStride apart; null if there is no room
 };
+constexpr int kTurnStride = 8;  // 256 bytes in all
 
 __device__ __forceinline__ int32_t num_pieces(int32_t len) {
     return len / kPieceMin < kMaxPieces ? len / kPieceMin : kMaxPieces;
@@ -621,6 +623,8 @@ __global__ __launch_bounds__(kListThreads) void k_backward_list(
     }
     __syncthreads();
     if (threadIdx.x == 0) ws.heads[blockIdx.x] = make_int4(count[0], count[1], p0, count[2]);
+    if (blockIdx.x == 0 && threadIdx.x < kXcds && ws.turns != nullptr)
+        ws.turns[threadIdx.x * kTurnStride] = 0;
     if (blockIdx.x == 0 && gridDim.x + threadIdx.x < ws.list_blocks)
         ws.heads[gridDim.x + threadIdx.x] = make_int4(0, 0, 0, 0);
 }
@@ -899,20 +903,21 @@ __device__ __forceinline__ void run_long(const float *__restrict__ grad, int32_t
     if (col < dim) sink_value(sink, u, dim, col, acc, v);
 }
 
-// Short segments: one lane group per segment, as the forward; wavefront
-// `wave` of `nwave`. Long ones are left to the chains: all of them without a
+// Short segments o < num, from `start` on: one lane group per segment, as the
+// forward; wavefront `wave` of `nwave`. Long ones are left to the chains: all of them without a
 // workspace, the covered ones with one (uncovered ones are summed here).
 template <int LANES, int CHUNKS>
 __device__ __forceinline__ void short_segments(const float *__restrict__ grad, int32_t dim,
                                                const int32_t *__restrict__ ids,
                                                const int32_t *__restrict__ offsets, int64_t num,
                                                const RowSink &sink, int64_t cap_pairs,
-                                               int64_t wave, int64_t nwave) {
+                                               int64_t wave, int64_t nwave,
+                                               int64_t start = 0) {
     constexpr int kGroups = kWave / LANES;
     const int lane = threadIdx.x & (kWave - 1);
     const int sub = lane & (LANES - 1);
     const int grp = lane / LANES;
-    for (int64_t o0 = wave * kGroups; o0 < num; o0 += nwave * kGroups) {
+    for (int64_t o0 = start + wave * kGroups; o0 < num; o0 += nwave * kGroups) {
         const int64_t o = o0 + grp;
         int32_t beg = 0, end = 0;
         bool mine = false;
@@ -966,6 +971,17 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 //   8 x 300k x 128    45.9  44.0  44.2               47.8  44.0  43.2
 // Against the short segments first and the chains after them, in a kernel of
 // five-wavefront workgroups: 82, 178, 402 and 71 us.
+//
+// Where a wavefront has kTurns * kTurnWindows windows of the sweep or more, it
+// takes the sweep in kTurns parts: its own share of the first, then whichever
+// shares of the others are next on its XCD's counter. Workgroups that start
+// late, when another stream's kernels hold their places, then cost a part of
+// the sweep, not the whole of it once more (32 tables of 1M x 256 with the
+// next batch's cast on a side stream: 235 steps/s without, 289 with; backward +
+// update alone 2190 us without, 2162 with). Shorter sweeps end before another
+// stream's kernels do, and would pay the counters' round trips (0.5 us each).
+constexpr int kTurns = 8;
+constexpr int kTurnWindows = 32;
 template <int LANES, int CHUNKS>
 __global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : CHUNKS == 2 ? 5 : 2) void k_backward_rows(
     const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids,
@@ -1003,10 +1019,32 @@ __global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : CHUNKS == 2 ? 5 : 2) void
     const int32_t chain_rounds = int32_t(rounds < most ? rounds : most);
     const int32_t chain_blocks = chain_rounds * kXcds;
     if (int32_t(blockIdx.x) >= chain_blocks) {
-        short_segments<LANES, CHUNKS>(
-            grad, dim, ids, offsets, num, sink, ws.cap_pairs,
-            (int64_t(blockIdx.x) - chain_blocks) * kWaves + threadIdx.x / kWave,
-            (int64_t(gridDim.x) - chain_blocks) * kWaves);
+        const int32_t nwave = (int32_t(gridDim.x) - chain_blocks) * kWaves;
+        int32_t wave = (int32_t(blockIdx.x) - chain_blocks) * kWaves + w;
+        const int64_t window = int64_t(nwave) * (kWave / LANES);
+        const int32_t per_turn = int32_t((num + window - 1) / window / kTurns);
+        if (per_turn < kTurnWindows || ws.turns == nullptr || gridDim.x % kXcds != 0) {
+            short_segments<LANES, CHUNKS>(grad, dim, ids, offsets, num, sink, ws.cap_pairs, wave,
+                                          nwave);
+            return;
+        }
+        // turn 0 is the wavefront's own; the others as they come, of its XCD's
+        const int32_t mates = nwave / kXcds;
+        int32_t turn = 0;
+        do {
+            const int64_t start = turn * per_turn * window;
+            const int64_t end = turn < kTurns - 1 ? start + per_turn * window : num;
+            short_segments<LANES, CHUNKS>(grad, dim, ids, offsets, end, sink, ws.cap_pairs, wave,
+                                          nwave, start);
+            int32_t t = 0;
+            if ((threadIdx.x & (kWave - 1)) == 0)
+                t = __hip_atomic_fetch_add(ws.turns + blockIdx.x % kXcds * kTurnStride, 1,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            t = __builtin_amdgcn_readfirstlane(t);
+            turn = 1 + t / mates;
+            const int32_t mate = t % mates;
+            wave = (mate / kWaves * kXcds + blockIdx.x % kXcds) * kWaves + mate % kWaves;
+        } while (turn < kTurns);
         return;
     }
     const int32_t xcd = blockIdx.x % kXcds;
@@ -1120,7 +1158,7 @@ WsLayout ws_layout(int64_t cap, int32_t dim) {
 // kLongSegment pairs fit.
 SplitWs make_split_ws(void *ws, size_t bytes, int32_t dim) {
     SplitWs s{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0,
-              (dim + kPartCols - 1) / kPartCols};
+              (dim + kPartCols - 1) / kPartCols, nullptr};
     if (ws == nullptr || ws_layout(kLongSegment, dim).total > bytes) return s;
     int64_t lo = kLongSegment, hi = (int64_t(1) << 31) - 1;
     while (lo < hi) {  // largest cap whose layout fits
@@ -1136,6 +1174,8 @@ SplitWs make_split_ws(void *ws, size_t bytes, int32_t dim) {
     s.partial = reinterpret_cast<float *>(p + l.partial);
     s.cap_pairs = lo;
     s.list_blocks = l.list_blocks;
+    // the start of the workspace, where the heads are if there are few
+    if (l.heads != 0) s.turns = reinterpret_cast<int32_t *>(p);
     return s;
 }
 
