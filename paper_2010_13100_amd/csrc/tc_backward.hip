@@ -564,16 +564,15 @@ __global__ __launch_bounds__(kLongThreads) void k_backward_long(
     }
 }
 
-// Lists the long segments, in an order of no consequence. Only segments inside the cover matter, and each
-// has at least one pair, so the first cap_pairs segments hold all of them.
+// Lists the long segments inside the cover, in an order of no consequence. Any
+// of the num segments may be one: those before it may be without pairs.
 constexpr int kListThreads = 1024;
 __global__ __launch_bounds__(kListThreads) void k_backward_list(
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
     int64_t num_out_cap, SplitWs ws) {
     __shared__ int32_t count[3];  // entries in big[], in longs[], pairs in both
     const int64_t u_dev = *num_out_dev;
-    int64_t num = u_dev < num_out_cap ? u_dev : num_out_cap;
-    num = num < ws.cap_pairs ? num : ws.cap_pairs;
+    const int64_t num = u_dev < num_out_cap ? u_dev : num_out_cap;
     // Ranges of equal size. Nothing past offsets[num] is read: the capacities
     // say nothing of the array's length. (Loads by the capacity, beside num's
     // and not after it, were no faster: 24.2 us against 24.1 for the step of 1
@@ -1194,8 +1193,7 @@ tc_status launch_backward(const float *grad, int64_t grad_rows, int32_t dim,
     const unsigned grid = grid_for(cap, rows_per_block, int64_t(device_cus()) * 8);
     unsigned all_blocks = grid;
     if (ws.cap_pairs > 0) {
-        const int64_t scanned = cap < ws.cap_pairs ? cap : ws.cap_pairs;
-        k_backward_list<<<grid_for(scanned, kListThreads, ws.list_blocks), kListThreads, 0, stream>>>(
+        k_backward_list<<<grid_for(cap, kListThreads, ws.list_blocks), kListThreads, 0, stream>>>(
             offsets, num_out_dev, cap, ws);
         const tc_status st = check_launch("k_backward_list");
         if (st != TC_OK) return st;

@@ -8,7 +8,8 @@ from tests import host_kernel as hk
 
 MAIN = r"""
 // num segments; cap segments of room, cap_pairs covered, blocks workgroups.
-// lens: 0 = of 1 to 3 pairs, with one of 48 or more now and then
+// of 1 to 3 pairs, with one of 48 or more now and then; `empty` percent
+// of them without pairs instead
 int main(int argc, char **argv) {
     const int64_t num = atoll(argv[1]), cap = atoll(argv[2]), cap_pairs = atoll(argv[3]);
     const int blocks = atoi(argv[4]), empty = atoi(argv[5]);
@@ -17,7 +18,7 @@ int main(int argc, char **argv) {
     auto next = [&] { return s = s * 1664525u + 1013904223u, s >> 8; };
     for (int64_t u = 0; u < num; ++u) {
         const uint32_t r = next() % 97;
-        int32_t len = r == 0 ? 48 + next() % 700 : r == 1 ? 2048 + next() % 9000 : 1 + r % 3;
+        int32_t len = r == 0 ? 48 + next() % 700 : r == 1 && !empty ? 2048 + next() % 9000 : 1 + r % 3;
         if (empty && int(next() % 100) < empty) len = 0;
         offs[u + 1] = offs[u] + len;
     }
@@ -32,8 +33,7 @@ int main(int argc, char **argv) {
     std::vector<int32_t> done((pairs / kSplitPairs + 2) * ws.parts, -1), turns(kXcds * kTurnStride);
     ws.heads = heads.data(), ws.big = big.data(), ws.longs = longs.data();
     ws.seg_done = done.data(), ws.turns = turns.data();
-    const int64_t scanned = SCANNED;
-    const int grid = int(std::max<int64_t>(1, std::min<int64_t>(blocks, (scanned + kListThreads - 1) / kListThreads)));
+    const int grid = int(std::max<int64_t>(1, std::min<int64_t>(blocks, (cap + kListThreads - 1) / kListThreads)));
     run_grid(grid, kListThreads, [&] { k_backward_list(Checked{offs.data(), num + 1}, &n, cap, ws); });
     // the entries, by the heads' slots, against the segments
     std::vector<int32_t> listed(num, 0);
@@ -78,13 +78,12 @@ def exe(tmp_path_factory):
     kernel = hk.block(src, "__global__ __launch_bounds__(kListThreads) void k_backward_list(")
     kernel = kernel.replace("const int32_t *__restrict__ offsets", "Checked offsets", 1)
     assert "Checked offsets" in kernel
-    # the segments that the host sizes the grid by, as launch_backward has it
-    scanned = src[src.index("const int64_t scanned = ") + len("const int64_t scanned = "):]
-    scanned = scanned[:scanned.index(";")]
+    # the grid, as launch_backward has it
+    assert "grid_for(cap, kListThreads, ws.list_blocks)" in src
     return hk.program(tmp_path_factory.mktemp("list"), [
         "constexpr int32_t kSplitPairs = 2048;\n", hk.const(internal, "kXcds"), consts,
         hk.block(src, "struct SplitWs {"), hk.block(src, "__device__ __forceinline__ int32_t num_pieces("),
-        kernel], MAIN.replace("SCANNED", scanned))
+        kernel], MAIN)
 
 
 # segments against the capacities: full, a few segments in room for many (the
@@ -97,3 +96,12 @@ def exe(tmp_path_factory):
     (3_000, 300_000, 10 ** 7, 256)])
 def test_reads_only_the_batch_s_offsets(exe, num, cap, cap_pairs, blocks):
     hk.run(exe, num, cap, cap_pairs, blocks, 0)
+
+
+# segments without pairs, more of them than the workspace covers pairs
+@pytest.mark.parametrize("num,cap_pairs,blocks,empty", [
+    (50_000, 6_000, 16, 99), (9_000, 4_000, 16, 98), (400_000, 100_000, 256, 99),
+    (2_500, 2_400, 16, 80)])
+def test_segments_without_pairs(exe, num, cap_pairs, blocks, empty):
+    out = hk.run(exe, num, num, cap_pairs, blocks, empty)
+    assert int(out.split()[0]) > 0
