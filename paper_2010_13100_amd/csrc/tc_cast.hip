@@ -106,6 +106,10 @@ __device__ __forceinline__ int32_t block_scan(int32_t v, int32_t *total) {
 struct alignas(16) TileRec {
     int32_t p0, p1, first, next, pstart, rowoff, s, pad;
 };
+// Tiles of `pairs` pairs. (Positions go up to 2^31 - 1: no sum here exceeds it.)
+__device__ __forceinline__ int32_t tiles_of(int32_t pairs) {
+    return pairs / kSortTile + (pairs % kSortTile != 0);
+}
 // ---------------------------------------------------------------------------
 // 1. key build. The segments of the table-local sort, in LDS: segment s has
 // tiles [tstart[s], tstart[s+1]) and pairs [pstart[s], pstart[s+1]), and
@@ -126,7 +130,7 @@ __device__ int32_t seg_layout(SegLayout &L, const int32_t *__restrict__ bag_offs
         L.rowoff[t] = int32_t(table_row_offset[t]);
     }
     int32_t total;
-    const int32_t ts = block_scan<kBlock>((n_t + kSortTile - 1) / kSortTile, &total);
+    const int32_t ts = block_scan<kBlock>(tiles_of(n_t), &total);
     if (t < num_tables) {
         L.tstart[t] = ts;
         L.pstart[t] = p0;
@@ -157,7 +161,7 @@ __device__ TileRec tile_record(const SegLayout &L, int32_t num_tables, int32_t t
         r.rowoff = L.rowoff[sg];
         r.p0 = L.pstart[sg] + (b - r.first) * kSortTile;
         const int32_t end = L.pstart[sg + 1];
-        r.p1 = r.p0 + kSortTile < end ? r.p0 + kSortTile : end;
+        r.p1 = end - r.p0 > kSortTile ? r.p0 + kSortTile : end;
     }
     return r;
 }
@@ -219,9 +223,9 @@ __device__ __forceinline__ void build_pairs(int64_t b, int64_t blocks,
     for (int64_t g = b * kGroups + threadIdx.x / kLanes; g < num_bags; g += blocks * kGroups) {
         const int32_t beg = bag_offsets[g], end = bag_offsets[g + 1];
         const int64_t base = local ? 0 : table_row_offset[g / bags_per_table];
-        for (int32_t j = beg + sub; j < end; j += kLanes) {
+        for (uint32_t j = beg + sub; j < uint32_t(end); j += kLanes) {  // may pass 2^31
             keys[j] = int32_t(base + indices[j]);
-            vals[j] = positions ? j : int32_t(g);
+            vals[j] = positions ? int32_t(j) : int32_t(g);
         }
     }
 }
@@ -277,7 +281,7 @@ __device__ __forceinline__ TileRec tile_of(int32_t b, int32_t tiles,
     TileRec r{0, 0, 0, 0, 0, 0, -1, 0};
     if (b >= tiles) return r;
     if (recs) return recs[b];
-    r.next = (n + kSortTile - 1) / kSortTile;
+    r.next = tiles_of(n);
     if (b < r.next) {
         r.s = 0;
         r.p0 = b * kSortTile;
@@ -819,7 +823,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_cast_small(
 #pragma unroll
         for (int i = 0; i < kSmallItems; ++i)
             if (start[i] < n) atomicAdd(&marks[start[i]], 1);
-        for (int32_t g = tid + kSmallPairs; g < num_bags; g += kSmallThreads) {
+        for (uint32_t g = tid + kSmallPairs; g < uint32_t(num_bags); g += kSmallThreads) {
             const int32_t b = bag_offsets[g];  // bags without pairs beyond the first 8192
             if (b < n) atomicAdd(&marks[b], 1);
         }
