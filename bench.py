@@ -94,11 +94,11 @@ KERNEL_NAMES = {
     "backward": ["k_backward_list", "k_backward_rows", "k_backward_short"],
     "backward_update": ["k_backward_list", "k_backward_rows", "k_backward_short"],
     "update": ["k_sparse_update"],
-    "cast": ["k_cast_small", "k_build_keys", "k_radix_hist", "k_radix_scatter",
-             "k_segments", "k_seg_count", "k_seg_write"],
+    "cast": ["k_cast_small", "k_build_keys", "k_radix_hist", "k_radix_scan",
+             "k_radix_scatter", "k_segments", "k_seg_count", "k_seg_write"],
     # the forward's bags run in the pair build's launch (or beside k_cast_small)
     "forward_cast": ["k_cast_small", "k_forward_build", "k_build_keys", "k_radix_hist",
-                     "k_radix_scatter", "k_segments", "k_seg_count", "k_seg_write", "k_forward"],
+                     "k_radix_scan", "k_radix_scatter", "k_segments", "k_seg_count", "k_seg_write", "k_forward"],
 }
 
 

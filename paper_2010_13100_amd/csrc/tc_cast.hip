@@ -8,6 +8,7 @@
 //     the key bits that can be set. Each pass is
 //       k_radix_hist    per-tile digit counts (LDS histograms), and their
 //                       sums over full groups of kGroupTiles tiles
+//       k_radix_scan    for long segments: prefixes of those sums
 //       k_radix_scatter stable scatter: the tile's place in each digit from
 //                       the counts of the tiles before it; a wave finds the
 //                       lanes holding equal digits with ballots, counts them
@@ -25,7 +26,8 @@
 // What bounds it at a batch of a million pairs is not bandwidth (a pass moves
 // 20 bytes per pair, 4 us) but the number of launches and, in each, a chain of
 // dependent steps of 4-10 us that every workgroup goes through once: so few
-// passes with wide digits, and no kernel between a histogram and its scatter.
+// passes with wide digits, and no kernel between a histogram and its scatter
+// until segments are long.
 // Measured (us, the cast's kernels): 8 tables of 1M rows, 1.3M pairs: 49,
 // against 70 with three passes of 7-bit digits over 2048-pair tiles with a
 // scan kernel each; 16 tables, 91k pairs each: 61 against 84; 13 tables, 139k
@@ -166,16 +168,20 @@ __device__ TileRec tile_record(const SegLayout &L, int32_t num_tables, int32_t t
     return r;
 }
 
-// The records of all num_tile_slots tile slots, written by one workgroup.
+// The records of all num_tile_slots tile slots, written by one workgroup, and
+// the segments' first tiles to seg_first (if not null).
 __device__ void write_tile_records(const int32_t *__restrict__ bag_offsets,
                                    const int64_t *__restrict__ table_row_offset,
                                    int64_t num_bags, int32_t bags_per_table, int32_t num_tables,
-                                   TileRec *__restrict__ tiles, int32_t num_tile_slots) {
+                                   TileRec *__restrict__ tiles, int32_t num_tile_slots,
+                                   int32_t *__restrict__ seg_first) {
     __shared__ SegLayout L;
     const int32_t total = seg_layout(L, bag_offsets, table_row_offset, num_bags, bags_per_table,
                                      num_tables);
     for (int32_t b = threadIdx.x; b < num_tile_slots; b += kBlock)
         tiles[b] = tile_record(L, num_tables, total, b);
+    if (seg_first)
+        for (int32_t t = threadIdx.x; t <= num_tables; t += kBlock) seg_first[t] = L.tstart[t];
 }
 
 // Where the sort's bookkeeping is, for the kernels before its first pass:
@@ -187,6 +193,7 @@ struct SortPrep {
     int64_t group_words;
     int32_t *state;  // of the segment build, cleared too
     int64_t state_words;
+    int32_t *seg_first;  // for k_radix_scan (null: it does not run)
 };
 // The share of workgroup `b` of `blocks` in that; workgroup 0 also writes the
 // records.
@@ -201,7 +208,7 @@ __device__ __forceinline__ void prepare_sort(const SortPrep &sp, int64_t b, int6
         sp.state[i] = 0;
     if (sp.recs && b == 0)
         write_tile_records(bag_offsets, table_row_offset, num_bags, bags_per_table, num_tables,
-                           sp.recs, sp.tile_slots);
+                           sp.recs, sp.tile_slots, sp.seg_first);
 }
 
 // (src, dst) pairs by a walk over the bags, and the share of workgroup `b` of
@@ -403,11 +410,52 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(
     }
 }
 
-// 2b. stable scatter of one tile. Where the tile's run of each digit goes
-// comes straight from the counts: the segment's full groups, and at most two
-// partial groups tile by tile, so no scan kernel runs between the histogram
-// and this one, and a segment of any length costs at most its groups and 32
-// loads. Within a wavefront the lanes holding equal digits are found with
+// 2b. where segments can be long (scan_groups): in those of more than
+// kScanGroups full groups, the groups' digit sums become their inclusive
+// prefixes over the groups, in place, so that the scatter reads two rows
+// however long its segment is (all rows, read by every tile, cost the square of
+// the segment's length). A workgroup takes 32 digits of every gridDim.y-th
+// segment, in chunks of rows side by side. seg_first: the segments' first tiles
+// and the last one's end; null for one segment of `tiles` tiles.
+constexpr int kScanGroups = 8;
+constexpr int kScanThreads = 1024;
+constexpr int kScanDigits = 32, kScanChunks = kScanThreads / kScanDigits;
+__global__ __launch_bounds__(kScanThreads) void k_radix_scan(
+    int32_t *__restrict__ groups, int radix, const int32_t *__restrict__ seg_first,
+    int32_t num_segs, int32_t tiles) {
+    __shared__ int32_t sums[kScanChunks][kScanDigits];
+    const int32_t d = threadIdx.x % kScanDigits, chunk = threadIdx.x / kScanDigits;
+    const int32_t digit = blockIdx.x * kScanDigits + d;
+    for (int32_t s = blockIdx.y; s < num_segs; s += gridDim.y) {  // uniform
+        const int32_t first = seg_first ? seg_first[s] : 0;
+        const int32_t full = ((seg_first ? seg_first[s + 1] : tiles) - first) / kGroupTiles;
+        if (full <= kScanGroups) continue;
+        int32_t *rows = groups + int64_t(first / kGroupTiles) * radix;
+        const int32_t per = (full + kScanChunks - 1) / kScanChunks;
+        const int32_t g0 = min(chunk * per, full), g1 = min(g0 + per, full);
+        int32_t sum = 0;
+        if (digit < radix)
+#pragma unroll 8
+            for (int32_t g = g0; g < g1; ++g) sum += rows[int64_t(g) * radix + digit];
+        sums[chunk][d] = sum;
+        __syncthreads();
+        int32_t run = 0;
+#pragma unroll
+        for (int k = 0; k < kScanChunks; ++k) run += k < chunk ? sums[k][d] : 0;
+        if (digit < radix)
+#pragma unroll 8
+            for (int32_t g = g0; g < g1; ++g) {
+                run += rows[int64_t(g) * radix + digit];
+                rows[int64_t(g) * radix + digit] = run;
+            }
+        __syncthreads();  // sums is written again
+    }
+}
+
+// 2c. stable scatter of one tile. Where the tile's run of each digit goes
+// comes straight from the counts: the segment's full groups (two rows of their
+// prefixes if k_radix_scan has run, else all of them), and at most two partial
+// groups tile by tile. Within a wavefront the lanes holding equal digits are found with
 // ballots; each reads the wave's running count of its digit and the lowest of
 // them then adds their number to it. The tile is then laid out in sorted order in LDS, keys and then
 // values, and written back thread by thread in that order, so neighbouring
@@ -419,7 +467,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const int32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
     int32_t *__restrict__ keys_out, int32_t *__restrict__ vals_out, int32_t n, int shift,
     const TileRec *__restrict__ recs, int32_t tiles, const uint32_t *__restrict__ counts,
-    const int32_t *__restrict__ groups, bool add_rowoff) {
+    const int32_t *__restrict__ groups, bool scanned, bool add_rowoff) {
     constexpr int R = 1 << BITS;
     constexpr int H = R / 2;  // words of two digits
     constexpr int WPT = H > kSortThreads ? H / kSortThreads : 1;  // consecutive ones per thread
@@ -450,7 +498,17 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
         if (tid * WPT < H) {
             const int32_t full = (tr.next - tr.first) / kGroupTiles;  // full groups
             const int32_t mine = (b - tr.first) / kGroupTiles;
-            for (int32_t g0 = 0; g0 < full; g0 += 8) {
+            const bool sums = scanned && full > kScanGroups;  // uniform
+            if (sums) {  // inclusive prefixes already
+                const int32_t *row = groups + int64_t(tr.first / kGroupTiles) * R + 2 * WPT * tid;
+#pragma unroll
+                for (int k = 0; k < 2 * WPT; ++k) {
+                    before[k] = row[int64_t(max(mine - 1, 0)) * R + k];
+                    total[k] = row[int64_t(full - 1) * R + k];
+                    before[k] = mine > 0 ? before[k] : 0;
+                }
+            }
+            for (int32_t g0 = 0; g0 < full && !sums; g0 += 8) {
                 int32_t c[8][2 * WPT];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
@@ -989,15 +1047,23 @@ __global__ void k_cast_empty(int32_t *seg_offsets, int32_t *num_unique) {
 // One LSD pass over `bits` (1..kMaxRadixBits) digit bits starting at `shift`.
 tc_status launch_radix_pass(int bits, const int32_t *kin, const int32_t *vin, int32_t *kout,
                             int32_t *vout, int32_t n, int shift, const TileRec *recs,
-                            uint32_t *counts, int32_t *groups, int32_t tiles, bool last,
+                            uint32_t *counts, int32_t *groups, int32_t tiles, bool scan,
+                            const int32_t *seg_first, int32_t num_segs, bool last,
                             hipStream_t stream) {
 #define TC_PASS_CASE(B)                                                                      \
     case B:                                                                                  \
         k_radix_hist<B><<<tile_grid(tiles), kSortThreads, 0, stream>>>(                      \
             kin, n, shift, recs, tiles, counts, groups);                                     \
         if (check_launch("k_radix_hist") != TC_OK) return TC_ERR_HIP;                        \
+        if (scan) {                                                                          \
+            k_radix_scan<<<dim3(((1 << B) + kScanDigits - 1) / kScanDigits,                  \
+                                num_segs < 8 ? num_segs : 8),                                \
+                           kScanThreads, 0, stream>>>(groups, 1 << B, seg_first, num_segs,   \
+                                                      (n - 1) / kSortTile + 1);              \
+            if (check_launch("k_radix_scan") != TC_OK) return TC_ERR_HIP;                    \
+        }                                                                                    \
         k_radix_scatter<B><<<tile_grid(tiles), kSortThreads, 0, stream>>>(                   \
-            kin, vin, kout, vout, n, shift, recs, tiles, counts, groups, last);              \
+            kin, vin, kout, vout, n, shift, recs, tiles, counts, groups, scan, last);        \
         return check_launch("k_radix_scatter");
     switch (bits) {
         TC_PASS_CASE(1)
@@ -1081,6 +1147,22 @@ inline SortDigits sort_digits(const CastPlan &p, int64_t n, int bits) {
         if (d.per_pass == 1 || d.counts_bytes + d.passes * d.group_words * 4 <= p.counts_bytes)
             return d;
     }
+}
+
+// Whether k_radix_scan runs in a sort of `tiles` tiles and num_segs segments,
+// whose own lengths only the device knows. Its launch takes 2.2 us a pass. Against
+// that stand the rows of group sums that the tiles read without it: tiles x
+// (groups of their segment). It runs from 2^14 rows at the mean length of a
+// segment, and from 2^17 (5.9M pairs) if one segment could have all pairs.
+// Measured (us of the cast, without and with; pairs): one table of 4M rows 87.9
+// and 87.2 (2.0M), 112 and 105 (2.2M), 203 and 159 (5M), 3290 and 932 (35M),
+// 21800 and 2740 (100M); 4 tables of 1M 100.9 and 100.8 (4M), 138.9 and 131.3
+// (6M); 32 tables of 1M 119.8 and 124.3 (5.2M), 434 and 428 (20M). One of
+// many tables having nearly all of up to 5.9M pairs is what the rule leaves: at
+// most 170 and 130.
+inline bool scan_groups(int64_t tiles, int32_t num_segs) {
+    const int64_t rows = tiles * (tiles / kGroupTiles);
+    return rows / num_segs >= 1 << 14 || rows >= 1 << 17;
 }
 
 // bits needed for keys in [0, rows)
@@ -1203,8 +1285,15 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
     const SortDigits digits = sort_digits(plan, num_pairs, bits);
     const int passes = digits.passes, per_pass = digits.per_pass;
     int32_t *groups = reinterpret_cast<int32_t *>(ws + plan.off_counts + digits.counts_bytes);
-    const SortPrep prep{recs,  sort_tiles,     groups, int64_t(digits.group_words) * passes,
-                        state, plan.seg_tiles <= kOneLaunchTiles ? plan.seg_tiles + 1 : 0};
+    const int32_t num_segs = local ? num_tables : 1;
+    const bool scan = scan_groups(plan.seg_tiles, num_segs);
+    // behind the records: their area has room for one per 2048 pairs, twice the
+    // tiles, and a scanned sort has 512 tiles or more
+    static_assert(511 * sizeof(TileRec) >= (kMaxSegTables + 1) * sizeof(int32_t));
+    int32_t *seg_first = scan && local ? reinterpret_cast<int32_t *>(recs + sort_tiles) : nullptr;
+    const SortPrep prep{recs,   sort_tiles, groups,   int64_t(digits.group_words) * passes,
+                        state,  plan.seg_tiles <= kOneLaunchTiles ? plan.seg_tiles + 1 : 0,
+                        seg_first};
     if (fwd) {
         // the pair build's workgroups, then the forward's, in one launch
         const int64_t per_block = int64_t(kBlock / kWave) * (kWave / shape.lanes);
@@ -1245,8 +1334,9 @@ tc_status cast_impl(const char *what, bool positions, const int64_t *table_row_o
                        : last            ? static_cast<void *>(vout)
                                          : static_cast<void *>(casted_src);
         tc_status st = launch_radix_pass(pb, kin, vin, kout, vdst, int32_t(num_pairs), shift,
-                                         recs, static_cast<uint32_t *>(counts), groups + p * digits.group_words,
-                                         sort_tiles, last, stream);
+                                         recs, static_cast<uint32_t *>(counts),
+                                         groups + p * digits.group_words, sort_tiles, scan,
+                                         seg_first, num_segs, last, stream);
         if (st != TC_OK) return st;
         // next pass reads what this one wrote
         int32_t *tk = kin, *tv = vin;

@@ -28,6 +28,23 @@ def test_groups_of_tiles(tiles):
           seed=tiles)
 
 
+# sorts whose group sums are scanned (one segment: from 512 tiles; three: from
+# 887) and not, table-local and global
+@pytest.mark.parametrize("groups", [31, 32, 55, 56])
+def test_long_segments(groups):
+    n = groups * GROUP * TILE + 37
+    check(f"{groups} groups", [3000, 40_000, 70], [TILE + 1, n, 5], bags_per_table=2000,
+          seed=groups)
+
+
+# in a scanned sort, segments on both sides of the 8 groups that are added up
+# one by one
+def test_segments_of_a_scanned_sort():
+    n = GROUP * TILE
+    check("scanned sort", [900, 5000, 30, 70_000], [8 * n + 5, 9 * n, 60 * n - 1, 9],
+          bags_per_table=999, seed=1)
+
+
 # the segment build in one launch (up to 96 tiles) and in two
 @pytest.mark.parametrize("pairs", [95 * TILE + 1, 96 * TILE, 96 * TILE + 1])
 def test_segment_build_launches(pairs):
