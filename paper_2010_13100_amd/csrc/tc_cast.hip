@@ -1129,6 +1129,16 @@ inline CastPlan cast_plan(int64_t n, int32_t num_tables) {
 // that (n words), as with many more tables than full tiles, they go into the
 // plan's own area. The group sums, one set per pass, are there in any case.
 // The fewest passes that fit are taken; those of 1 bit always do.
+//
+// Digits of kMaxRadixBits bits are for up to kWideTiles tiles, as many as the
+// scatter's workgroups of that width that are resident at once (two per CU): a
+// second round of them takes longer than a third pass of 7 or 8 bits, which keys
+// of 21 and 22 bits have instead. Measured (us of the cast, in two and in three
+// passes; pairs): one table of 4M rows 43.6 and 44.7 (0.4M), 60.0 and 56.6
+// (1.0M), 88.0 and 72.4 (2.0M), 104 and 88.5 (2.2M), 158 and 120 (5M), 2680 and
+// 2000 (100M); of 2M rows 54.4 and 55.2 (1.0M), 77.2 and 71.2 (2.0M), 92.0 and
+// 86.5 (2.2M); 16 ragged tables of up to 2M, Zipf lookups: 57.4 and 60.6 (1.4M).
+constexpr int64_t kWideTiles = 512;
 struct SortDigits {
     int passes, per_pass;
     bool own_counts;      // counts in the plan's area
@@ -1137,7 +1147,8 @@ struct SortDigits {
 };
 inline SortDigits sort_digits(const CastPlan &p, int64_t n, int bits) {
     SortDigits d{};
-    for (d.passes = (bits + kMaxRadixBits - 1) / kMaxRadixBits;; ++d.passes) {
+    const int most = p.seg_tiles <= kWideTiles ? kMaxRadixBits : kMaxRadixBits - 1;
+    for (d.passes = (bits + most - 1) / most;; ++d.passes) {
         d.per_pass = (bits + d.passes - 1) / d.passes;
         const size_t radix = size_t(1) << d.per_pass;
         const size_t counts = size_t(p.sort_tiles) * radix * 2;
@@ -1154,10 +1165,10 @@ inline SortDigits sort_digits(const CastPlan &p, int64_t n, int bits) {
 // that stand the rows of group sums that the tiles read without it: tiles x
 // (groups of their segment). It runs from 2^14 rows at the mean length of a
 // segment, and from 2^17 (5.9M pairs) if one segment could have all pairs.
-// Measured (us of the cast, without and with; pairs): one table of 4M rows 87.9
-// and 87.2 (2.0M), 112 and 105 (2.2M), 203 and 159 (5M), 3290 and 932 (35M),
-// 21800 and 2740 (100M); 4 tables of 1M 100.9 and 100.8 (4M), 138.9 and 131.3
-// (6M); 32 tables of 1M 119.8 and 124.3 (5.2M), 434 and 428 (20M). One of
+// Measured (us of the cast, without and with; pairs): one table of 4M rows 72.5
+// and 76.7 (2.0M), 91.7 and 88.9 (2.2M), 149.5 and 120.3 (5M), 2239 and 684
+// (35M), 15500 and 2000 (100M); 4 tables of 2M 82.5 and 86.9 (3M), 119.2 and
+// 117.2 (5M); 32 tables of 1M 119.8 and 124.3 (5.2M), 434 and 428 (20M). One of
 // many tables having nearly all of up to 5.9M pairs is what the rule leaves: at
 // most 170 and 130.
 inline bool scan_groups(int64_t tiles, int32_t num_segs) {

@@ -28,6 +28,14 @@ def test_groups_of_tiles(tiles):
           seed=tiles)
 
 
+# digits of 11 bits up to 512 tiles, of 10 at most above
+@pytest.mark.parametrize("bits", [11, 21, 22, 31])
+@pytest.mark.parametrize("tiles", [512, 513])
+def test_widest_digits(bits, tiles):
+    check(f"{bits} bits, {tiles} tiles", [2 ** bits - 1], [tiles * TILE], bags_per_table=700,
+          seed=bits + tiles, bounds=[0])
+
+
 # sorts whose group sums are scanned (one segment: from 512 tiles; three: from
 # 887) and not, table-local and global
 @pytest.mark.parametrize("groups", [31, 32, 55, 56])
