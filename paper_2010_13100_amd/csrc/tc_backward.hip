@@ -630,6 +630,29 @@ __global__ __launch_bounds__(kListThreads) void k_backward_list(
         ws.heads[gridDim.x + threadIdx.x] = make_int4(0, 0, 0, 0);
 }
 
+// The chain over ids sid[0..len) for one wavefront with 64-bit addresses, for
+// segments whose rows no buffer window holds: kFarRows rows are on their way at
+// once. Measured (us of the call; segments spread over 2.4 GB): 4000 of 48 to 79
+// rows of 1024 floats 756 row after row, 209 with 32 at a time (184 if the lane
+// groups of the short segments had them); of 80 to 200 1650 and 411; of 600 to
+// 900 11800 and 2260.
+constexpr int kFarRows = 32;
+__device__ __forceinline__ float far_chain(const float *__restrict__ grad, int32_t dim,
+                                           const int32_t *__restrict__ sid, int32_t len,
+                                           int32_t col) {
+    const float *colp = grad + min(col, dim - 1);
+    float acc = 0.f;
+    for (uint32_t k = 0; k < uint32_t(len); k += kFarRows) {
+        float row[kFarRows];
+#pragma unroll
+        for (uint32_t i = 0; i < kFarRows; ++i)
+            row[i] = colp[int64_t(sid[min(k + i, uint32_t(len) - 1)]) * dim];
+#pragma unroll
+        for (uint32_t i = 0; i < kFarRows; ++i) acc = k + i < uint32_t(len) ? acc + row[i] : acc;
+    }
+    return acc;
+}
+
 // The ordered chain over ids[beg, beg + len) for one wavefront, lane l owning
 // column l of the part: kDepth row loads of 4 bytes per lane are in flight,
 // one register each; each is added and replaced by the load of the row kDepth
@@ -664,14 +687,11 @@ __device__ __forceinline__ float wave_chain(const float *__restrict__ grad, int3
         const int32_t end = __builtin_amdgcn_readfirstlane(sid[len - 1]);
         span = uint64_t(end - first + 1) * uint64_t(row_bytes);
     }
-    float acc = 0.f;
-    if (span > uint64_t(kOutOfRange) || len >= (1 << 28)) {
-        // as in run_chain: 64-bit addresses
+    if (span > uint64_t(kOutOfRange) || len >= (1 << 28)) {  // as in run_chain
         last();
-        const float *colp = grad + (col < dim ? col : dim - 1);
-        for (int32_t k = 0; k < len; ++k) acc = acc + colp[int64_t(sid[k]) * dim];
-        return acc;
+        return far_chain(grad, dim, sid, len, col);
     }
+    float acc = 0.f;
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(grad + int64_t(first) * dim), 0, int32_t(span), kBufferWord3);
     // lanes past the row's columns read its last one (a row's offset, in the
@@ -750,15 +770,10 @@ __device__ __forceinline__ float block_chain(float (&hand)[kWave], const float *
         const int32_t last = __builtin_amdgcn_readfirstlane(sid[len - 1]);
         span = uint64_t(last - first + 1) * uint64_t(row_bytes);
     }
+    if (span > uint64_t(kOutOfRange) || len >= (1 << 28))
+        // as in run_chain; one wavefront, no barriers
+        return w == kWgWaves - 1 ? far_chain(grad, dim, sid, len, col) : 0.f;
     float acc = 0.f;
-    if (span > uint64_t(kOutOfRange) || len >= (1 << 28)) {
-        // as in run_chain: 64-bit addresses, one wavefront, no barriers
-        if (w == kWgWaves - 1) {
-            const float *colp = grad + min(col, dim - 1);
-            for (int32_t k = 0; k < len; ++k) acc = acc + colp[int64_t(sid[k]) * dim];
-        }
-        return acc;
-    }
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(grad + int64_t(first) * dim), 0, int32_t(span), kBufferWord3);
     const int32_t lane_bytes = min(col, dim - 1) * 4;
@@ -984,7 +999,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 constexpr int kTurns = 8;
 constexpr int kTurnWindows = 32;
 template <int LANES, int CHUNKS>
-__global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : CHUNKS == 2 ? 5 : 2) void k_backward_rows(
+__global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : 7 - CHUNKS) void k_backward_rows(
     const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
     int64_t num_out_cap, RowSink sink, SplitWs ws, int32_t grad_bytes,
