@@ -971,14 +971,20 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 // others the short segments. Chains of neighbouring segments (of one table,
 // sharing its rows of grad) are put on one XCD, workgroups going round-robin
 // over the XCDs, for the sake of its L2; any other mapping gives the same
-// results. All workgroups are resident at once: more would sweep the short
-// segments in uneven windows (32 tables of 1M x 256: 2.42 ms with half as many
-// workgroups again, 2.14 ms with these).
+// results. Up to 512 columns all workgroups are resident at once, unless chains
+// take more than half of those places: more would sweep the short segments in
+// uneven windows (32 tables of 1M x 256: 2.42 ms with half as many workgroups
+// again, 2.14 ms with these; a million segments of 1 or 2 pairs, 320 columns 601
+// us with 8 workgroups per CU, 5 of them resident, and 550 with 5, 512 columns
+// 753 and 685). Chains are better off with the 8 (20 thousand segments of 1 to 90
+// pairs, 260 columns: 146 us, and 160 with 5), and wider rows, whose windows are
+// few, too (50 thousand segments of 1 to 20 pairs, 1024 columns: 274 us, and 282
+// with the 3 that are resident; 576 columns 123 and 127).
 // The chains' share of the workgroups is that of their pairs among all work,
 // with kSegmentCost pairs for each segment and kChainCost for each chain (8 x
 // 300k x 128, where many chains are short: 49.7 us without), so that both
 // parts end together,
-// but at least one workgroup per CU (min_chain_blocks): few long chains are
+// but at least one workgroup per CU: few long chains are
 // bound by their number of wavefronts. Measured (us, the kernel):
 //   kSegmentCost        4    12    36      min per CU  1/2     1     2
 //   8 x 1M x 64       57.9  55.5  55.6               55.7  55.5  59.3
@@ -998,12 +1004,13 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 // stream's kernels do, and would pay the counters' round trips (0.5 us each).
 constexpr int kTurns = 8;
 constexpr int kTurnWindows = 32;
+// Workgroups on a CU (wavefronts on a SIMD) by float4 chunks per lane.
+constexpr int rows_per_cu(int chunks) { return chunks == 1 ? 8 : 7 - chunks; }
 template <int LANES, int CHUNKS>
-__global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : 7 - CHUNKS) void k_backward_rows(
+__global__ __launch_bounds__(kBlock, rows_per_cu(CHUNKS)) void k_backward_rows(
     const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
-    int64_t num_out_cap, RowSink sink, SplitWs ws, int32_t grad_bytes,
-    int32_t min_chain_blocks) {
+    int64_t num_out_cap, RowSink sink, SplitWs ws, int32_t grad_bytes, int32_t cus) {
     constexpr int kWaves = kBlock / kWave;
     static_assert(kBlock == kListBlocks, "one head per thread");
     __shared__ ListIndex big, longs;
@@ -1031,15 +1038,22 @@ __global__ __launch_bounds__(kBlock, CHUNKS == 1 ? 8 : 7 - CHUNKS) void k_backwa
     const float chains = float(chain_pairs) + kChainCost * float(nbig + nlong);
     const int32_t share =
         int32_t(float(gridDim.x) * chains / (chains + kSegmentCost * float(num) + 1.f));
-    const int32_t most = min(max(share, min_chain_blocks), int32_t(gridDim.x) * 7 / 8) / kXcds;
+    const int32_t most = min(max(share, cus), int32_t(gridDim.x) * 7 / 8) / kXcds;
     const int32_t chain_rounds = int32_t(rounds < most ? rounds : most);
     const int32_t chain_blocks = chain_rounds * kXcds;
     if (int32_t(blockIdx.x) >= chain_blocks) {
-        const int32_t nwave = (int32_t(gridDim.x) - chain_blocks) * kWaves;
+        int32_t short_blocks = int32_t(gridDim.x) - chain_blocks;
+        if (CHUNKS == 2) {  // the resident ones, with the chains' unless those are many
+            const int32_t resident = cus * rows_per_cu(CHUNKS);
+            short_blocks = min(short_blocks, chain_blocks <= resident / 2 ? resident - chain_blocks
+                                                                          : resident);
+            if (int32_t(blockIdx.x) >= chain_blocks + short_blocks) return;
+        }
+        const int32_t nwave = short_blocks * kWaves;
         int32_t wave = (int32_t(blockIdx.x) - chain_blocks) * kWaves + w;
         const int64_t window = int64_t(nwave) * (kWave / LANES);
         const int32_t per_turn = int32_t((num + window - 1) / window / kTurns);
-        if (per_turn < kTurnWindows || ws.turns == nullptr || gridDim.x % kXcds != 0) {
+        if (per_turn < kTurnWindows || ws.turns == nullptr || short_blocks % kXcds != 0) {
             short_segments<LANES, CHUNKS>(grad, dim, ids, offsets, num, sink, ws.cap_pairs, wave,
                                           nwave);
             return;
