@@ -972,7 +972,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 // sharing its rows of grad) are put on one XCD, workgroups going round-robin
 // over the XCDs, for the sake of its L2; any other mapping gives the same
 // results. Up to 512 columns all workgroups are resident at once, unless chains
-// take more than half of those places: more would sweep the short segments in
+// take more than half of those places or the sweep is cut (below): more would sweep the short segments in
 // uneven windows (32 tables of 1M x 256: 2.42 ms with half as many workgroups
 // again, 2.14 ms with these; a million segments of 1 or 2 pairs, 320 columns 601
 // us with 8 workgroups per CU, 5 of them resident, and 550 with 5, 512 columns
@@ -994,23 +994,36 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 // Against the short segments first and the chains after them, in a kernel of
 // five-wavefront workgroups: 82, 178, 402 and 71 us.
 //
-// Where a wavefront has kTurns * kTurnWindows windows of the sweep or more, it
-// takes the sweep in kTurns parts: its own share of the first, then whichever
-// shares of the others are next on its XCD's counter. Workgroups that start
-// late, when another stream's kernels hold their places, then cost a part of
-// the sweep, not the whole of it once more (32 tables of 1M x 256 with the
-// next batch's cast on a side stream: 235 steps/s without, 289 with; backward +
-// update alone 2190 us without, 2162 with). Shorter sweeps end before another
-// stream's kernels do, and would pay the counters' round trips (0.5 us each).
+// A sweep of kTurns * kTurnWindows windows or more is cut into kTurns parts. The
+// workgroups take a share of the first part each, by position, and kTurns - 1
+// times as many follow them, whose wavefronts take the shares of the others as
+// they are next on their XCD's counter. Workgroups that start late, when another
+// stream's kernels hold their places, then cost a part of the sweep, not the whole
+// of it once more; and another stream's kernels find places when a part ends, not
+// when the sweep does. Measured, 32 tables of 1M x 256 (steps/s, the next batch's
+// cast on a side stream beside the backward, beside the whole step, and without
+// a side stream): one sweep 235, 228 and 292; parts taken in turn by workgroups
+// that stay 288.6, 293.1 and 297.8; by workgroups that end with their share
+// 296.4, 296.1 and 299.0. Shorter sweeps end before another stream's kernels do,
+// and would pay for the counters (0.5 us a share). A launch made for such a sweep
+// whose batch turns out short takes 4 us for the workgroups it has no use for (a
+// thousand segments in room for 5.2 million: 8.7 and 12.7 us).
 constexpr int kTurns = 8;
 constexpr int kTurnWindows = 32;
 // Workgroups on a CU (wavefronts on a SIMD) by float4 chunks per lane.
 constexpr int rows_per_cu(int chunks) { return chunks == 1 ? 8 : 7 - chunks; }
+// Whether the sweep of `num` segments by `blocks` workgroups is cut into parts.
+template <int LANES>
+constexpr bool sweep_in_parts(int64_t num, int32_t blocks) {
+    const int64_t window = int64_t(blocks) * (kBlock / LANES);
+    return (num + window - 1) / window >= kTurns * kTurnWindows && blocks % kXcds == 0;
+}
 template <int LANES, int CHUNKS>
 __global__ __launch_bounds__(kBlock, rows_per_cu(CHUNKS)) void k_backward_rows(
     const float *__restrict__ grad, int32_t dim, const int32_t *__restrict__ ids,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ num_out_dev,
-    int64_t num_out_cap, RowSink sink, SplitWs ws, int32_t grad_bytes, int32_t cus) {
+    int64_t num_out_cap, RowSink sink, SplitWs ws, int32_t grad_bytes, int32_t cus,
+    int32_t blocks) {
     constexpr int kWaves = kBlock / kWave;
     static_assert(kBlock == kListBlocks, "one head per thread");
     __shared__ ListIndex big, longs;
@@ -1019,6 +1032,10 @@ __global__ __launch_bounds__(kBlock, rows_per_cu(CHUNKS)) void k_backward_rows(
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t u_dev = *num_out_dev;
     const int64_t num = u_dev < num_out_cap ? u_dev : num_out_cap;
+    // the sweep in parts, if the launch has workgroups for the later ones
+    const bool later = int32_t(blockIdx.x) >= blocks;
+    const bool parts = int32_t(gridDim.x) > blocks && sweep_in_parts<LANES>(num, blocks);
+    if (later && !parts) return;
     const int t = threadIdx.x;  // the lists' heads, one per thread
     const int4 h = t < ws.list_blocks ? ws.heads[t] : make_int4(0, 0, 0, 0);
     int32_t before[3] = {h.x, h.y, h.w}, total[3];
@@ -1037,13 +1054,13 @@ __global__ __launch_bounds__(kBlock, rows_per_cu(CHUNKS)) void k_backward_rows(
     const int64_t rounds = rbig + rlong;
     const float chains = float(chain_pairs) + kChainCost * float(nbig + nlong);
     const int32_t share =
-        int32_t(float(gridDim.x) * chains / (chains + kSegmentCost * float(num) + 1.f));
-    const int32_t most = min(max(share, cus), int32_t(gridDim.x) * 7 / 8) / kXcds;
+        int32_t(float(blocks) * chains / (chains + kSegmentCost * float(num) + 1.f));
+    const int32_t most = min(max(share, cus), blocks * 7 / 8) / kXcds;
     const int32_t chain_rounds = int32_t(rounds < most ? rounds : most);
     const int32_t chain_blocks = chain_rounds * kXcds;
     if (int32_t(blockIdx.x) >= chain_blocks) {
-        int32_t short_blocks = int32_t(gridDim.x) - chain_blocks;
-        if (CHUNKS == 2) {  // the resident ones, with the chains' unless those are many
+        int32_t short_blocks = blocks - chain_blocks;
+        if (CHUNKS == 2 && !parts) {  // the resident ones, unless chains have most places
             const int32_t resident = cus * rows_per_cu(CHUNKS);
             short_blocks = min(short_blocks, chain_blocks <= resident / 2 ? resident - chain_blocks
                                                                           : resident);
@@ -1051,21 +1068,19 @@ __global__ __launch_bounds__(kBlock, rows_per_cu(CHUNKS)) void k_backward_rows(
         }
         const int32_t nwave = short_blocks * kWaves;
         int32_t wave = (int32_t(blockIdx.x) - chain_blocks) * kWaves + w;
-        const int64_t window = int64_t(nwave) * (kWave / LANES);
-        const int32_t per_turn = int32_t((num + window - 1) / window / kTurns);
-        if (per_turn < kTurnWindows || ws.turns == nullptr || short_blocks % kXcds != 0) {
+        if (!parts) {
             short_segments<LANES, CHUNKS>(grad, dim, ids, offsets, num, sink, ws.cap_pairs, wave,
                                           nwave);
             return;
         }
-        // turn 0 is the wavefront's own; the others as they come, of its XCD's
-        const int32_t mates = nwave / kXcds;
+        // part 0 is taken by position, of the others what is next on the XCD's
+        // counter: each XCD has nwave / kXcds shares of a part, and wavefronts
+        // for kTurns - 1 parts or more come later
+        const int64_t window = int64_t(nwave) * (kWave / LANES);
+        const int64_t per_turn = (num + window - 1) / window / kTurns * window;
         int32_t turn = 0;
-        do {
-            const int64_t start = turn * per_turn * window;
-            const int64_t end = turn < kTurns - 1 ? start + per_turn * window : num;
-            short_segments<LANES, CHUNKS>(grad, dim, ids, offsets, end, sink, ws.cap_pairs, wave,
-                                          nwave, start);
+        if (later) {
+            const int32_t mates = nwave / kXcds;
             int32_t t = 0;
             if ((threadIdx.x & (kWave - 1)) == 0)
                 t = __hip_atomic_fetch_add(ws.turns + blockIdx.x % kXcds * kTurnStride, 1,
@@ -1074,7 +1089,11 @@ __global__ __launch_bounds__(kBlock, rows_per_cu(CHUNKS)) void k_backward_rows(
             turn = 1 + t / mates;
             const int32_t mate = t % mates;
             wave = (mate / kWaves * kXcds + blockIdx.x % kXcds) * kWaves + mate % kWaves;
-        } while (turn < kTurns);
+            if (turn >= kTurns) return;
+        }
+        short_segments<LANES, CHUNKS>(grad, dim, ids, offsets,
+                                      turn < kTurns - 1 ? (turn + 1) * per_turn : num, sink,
+                                      ws.cap_pairs, wave, nwave, turn * per_turn);
         return;
     }
     const int32_t xcd = blockIdx.x % kXcds;
@@ -1234,11 +1253,13 @@ tc_status launch_backward(const float *grad, int64_t grad_rows, int32_t dim,
     bool launched = false;
 #define TC_BWD_CASE(L, C)                                                                    \
     if (!launched && s.lanes == L && s.chunks == C) {                                        \
-        if (ws.cap_pairs > 0)                                                                \
-            k_backward_rows<L, C><<<all_blocks, kBlock, 0, stream>>>(                        \
-                grad, dim, ids, offsets, num_out_dev, cap, out, ws, grad_bytes,              \
-                device_cus());                                                               \
-        else                                                                                 \
+        if (ws.cap_pairs > 0) {                                                              \
+            const bool parts = ws.turns && sweep_in_parts<L>(cap, int32_t(all_blocks));      \
+            k_backward_rows<L, C><<<parts ? kTurns * all_blocks : all_blocks, kBlock, 0,     \
+                                    stream>>>(grad, dim, ids, offsets, num_out_dev, cap,     \
+                                              out, ws, grad_bytes, device_cus(),             \
+                                              int32_t(all_blocks));                          \
+        } else                                                                               \
             k_backward_short<L, C><<<grid, kBlock, 0, stream>>>(grad, dim, ids, offsets,     \
                                                                 num_out_dev, cap, out);      \
         launched = true;                                                                     \
