@@ -1279,7 +1279,7 @@ tc_status launch_backward(const float *grad, int64_t grad_rows, int32_t dim,
         set_error("no backward kernel for dim %d", dim);
         return TC_ERR_UNSUPPORTED;
     }
-    const tc_status st = check_launch("k_backward_short");
+    const tc_status st = check_launch(ws.cap_pairs > 0 ? "k_backward_rows" : "k_backward_short");
     if (st != TC_OK || ws.cap_pairs > 0) return st;
     const int parts = (dim + kPartCols - 1) / kPartCols;
     const int ranges = kLongRanges / parts > 64 ? kLongRanges / parts : 64;
