@@ -1,7 +1,7 @@
 """tc_cast_index under table layouts the workloads do not cover, against the
 CPU oracle's Tensor Casting (Algorithm 2): tables of very different sizes,
 tables without pairs, per-table pair counts at and around the sort tile
-(2048 pairs), more tables than the table-local sort handles (global-row
+(4096 pairs), more tables than the table-local sort handles (global-row
 fallback), and the same batch cast with and without a table-size bound.
 Index outputs must be bit-exact in every case."""
 import numpy as np
@@ -13,7 +13,7 @@ from paper_2010_13100_amd import tc
 
 pytestmark = pytest.mark.gpu
 
-TILE = 2048
+TILE = 4096
 
 
 def make_case(table_rows, pairs_per_table, bags_per_table, seed):
@@ -136,8 +136,8 @@ def test_single_workgroup_cast_shares():
 
 def sparse_bags_case(num_tables, bags_per_table, pairs_per_table, rows, seed):
     """Bags mostly without pairs: each table's pairs sit in every 4th bag,
-    so a 2048-pair sort tile spans about 8192 bags (more than the pair build
-    stages per tile)."""
+    so that three of four groups of the pair build's lanes find none and a sort
+    tile spans up to 16 thousand bags."""
     rng = np.random.default_rng(seed)
     off = np.arange(num_tables + 1, dtype=np.int64) * rows
     lengths = np.zeros(num_tables * bags_per_table, np.int64)

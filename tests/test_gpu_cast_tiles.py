@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 TILE, GROUP = 4096, 16
 
 
-# 1..31 key bits: one to three passes of every width of digit
-@pytest.mark.parametrize("bits", [1, 2, 5, 7, 9, 10, 11, 12, 13, 15, 17, 19, 20, 21, 22, 23, 26])
+# 1..31 key bits, in one to three passes: every width of digit
+@pytest.mark.parametrize("bits", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 15, 17, 19, 20, 21, 22,
+                                  23, 26, 28, 31])
 def test_digit_widths(bits):
     check(f"{bits} bits", [2 ** bits - (bits > 3)], [3 * TILE - 5], bags_per_table=97, seed=bits,
           bounds=[0])

@@ -1,10 +1,11 @@
 """tc_embed_forward_cast (the forward gather-reduce and Tensor Casting in one
 call) against the CPU oracle: pooled rows bit for bit with the oracle's
 forward (Sec. II-B), the casted index bit for bit with its Tensor Casting
-(Algorithm 2). Row widths inside and outside the range whose forward runs in
-the cast's own launches (dim 36..256), batches on both sides of the
-single-workgroup cast (8192 pairs), table-local and global sorts, tables and
-bags without pairs, and more tables than the table-local sort takes."""
+(Algorithm 2). Row widths of every kernel of the forward that runs in the
+cast's launches (1 to 64 lanes a row, 1 to 4 chunks a lane), batches on both
+sides of the single-workgroup cast (8192 pairs; above 256 floats the forward
+runs before that one), table-local and global sorts, tables and bags without
+pairs, and more tables than the table-local sort takes."""
 import numpy as np
 import pytest
 import torch
@@ -56,16 +57,16 @@ def run_case(name, table_rows, pairs_per_table, bags_per_table, dim, seed, bound
     assert np.array_equal(cd[:n].cpu().numpy(), ref["casted_dst"][:n])
 
 
-@pytest.mark.parametrize("dim", [8, 36, 64, 128, 256, 260, 512])
+@pytest.mark.parametrize("dim", [4, 8, 16, 20, 36, 64, 128, 256, 260, 512, 516, 1024])
 def test_row_widths_multi_kernel(dim):
-    # 14.5k pairs: the radix-sort cast; dims 36..256 run the forward in the
-    # key build's launch, the others as a kernel of their own
+    # 14.5k pairs: the radix-sort cast, the forward in the pair build's launch
     run_case("unequal", [5, 1000, 3, 7000, 129], [40, 3000, 7, 9000, 2500], 5, dim, seed=dim)
 
 
-@pytest.mark.parametrize("dim", [8, 64, 128, 256, 512])
+@pytest.mark.parametrize("dim", [4, 8, 16, 32, 64, 128, 256, 260, 512, 768, 1024])
 def test_row_widths_single_workgroup(dim):
-    # 3k pairs: one cast workgroup, the forward's workgroups beside it
+    # 3k pairs: one cast workgroup, the forward's workgroups beside it (before
+    # it above 256 floats)
     run_case("small", [300, 1, 2000], [1000, 7, 2000], 11, dim, seed=dim + 1)
 
 
@@ -94,7 +95,7 @@ def test_no_pairs():
 
 
 def test_tiles_spanning_many_empty_bags():
-    # pairs in every 4th bag: a sort tile spans more bags than are staged
+    # pairs in every 4th bag
     case = sparse_bags_case(2, 40_000, 9_000, 5000, seed=8)
     run_case("sparse bags", [5000, 5000], None, 40_000, 64, seed=8, case=case)
     case = sparse_bags_case(3, 30_000, 7_000, 5000, seed=9)

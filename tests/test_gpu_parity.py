@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 
 W = wl.WORKLOADS
 # Each workload's distributions at sizes the oracle finishes in seconds; the
-# pair counts span several 2048-pair sort tiles and end in a ragged tile.
+# pair counts span several sort tiles (4096 pairs) and end in a ragged one.
 SMALL = {
     "c1": W["c1"],
     "c2-2x20k": W["c2"].scaled(name="c2-2x20k", num_tables=2, rows_per_table=20_000, batch=256),
