@@ -455,13 +455,13 @@ __global__ __launch_bounds__(kScanThreads) void k_radix_scan(
 // 2c. stable scatter of one tile. Where the tile's run of each digit goes
 // comes straight from the counts: the segment's full groups (two rows of their
 // prefixes if k_radix_scan has run, else all of them), and at most two partial
-// groups tile by tile. Within a wavefront the lanes holding equal digits are found with
-// ballots; each reads the wave's running count of its digit and the lowest of
-// them then adds their number to it. The tile is then laid out in sorted order in LDS, keys and then
-// values, and written back thread by thread in that order, so neighbouring
-// threads write neighbouring addresses of the same digit run (coalesced
-// stores instead of one scattered store per pair). With add_rowoff the keys
-// leave with the segment's row offset added.
+// groups tile by tile. Within a wavefront the lanes holding equal digits are
+// found with ballots; each reads the wave's running count of its digit and the
+// lowest of them then adds their number to it. The tile is then laid out in
+// sorted order in LDS, keys and then values, and written back thread by thread
+// in that order, so neighbouring threads write neighbouring addresses of the
+// same digit run (coalesced stores instead of one scattered store per pair).
+// With add_rowoff the keys leave with the segment's row offset added.
 template <int BITS>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const int32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
@@ -715,10 +715,11 @@ __device__ __forceinline__ void write_segments(const Heads &h, int64_t base, int
 // build), stored and loaded at agent scope, so nothing else needs ordering.
 // The workgroup of the last tile writes *num_unique.
 // The tickets cost 12 ns each, one after another, so two launches take less
-// time for many tiles. Measured (us of the kernels, against the two's): 35
-// tiles 5.0 and 6.6, 41 tiles 5.5 and 9.3, 160 tiles 7.4 and 9.1 (but the whole
-// step, where launches overlap, 61.8 and 60.8), 320 tiles 10.7 and 9.8, 1280
-// tiles 33.9 and 15.9.
+// time for many tiles. Measured (us in one launch and in two; tables of 1M x 64, the
+// cast and the whole step): 20 tiles 29.1 and 30.4, 50.0 and 50.9; 64 tiles 32.0
+// and 32.4, 76.2 and 76.4; 96 tiles 33.6 and 33.7, 97.3 and 97.0; 112 tiles 34.5
+// and 34.3, 105.7 and 105.2; 160 tiles 41.7 and 40.0, 141.6 and 140.0; 320 tiles
+// 56.7 and 52.4, 251 and 247.
 constexpr int kOneLaunchTiles = 96;
 __global__ __launch_bounds__(kSortThreads) void k_segments(
     const int32_t *__restrict__ keys, int64_t n, int32_t tiles, int32_t *__restrict__ state,
