@@ -230,13 +230,17 @@ size_t tc_backward_workspace_bytes(int64_t num_pairs, int32_t dim);
  * This is the coalesced gradient of table row unique_rows[u]; the expanded
  * per-pair gradient is never formed.
  *   grad_out   [num_bags x dim] fp32, one gradient per pooled output
+ *   seg_offsets, casted_src
+ *              read up to entry *num_unique and up to pair
+ *              seg_offsets[*num_unique] - 1; a segment may be empty (its row
+ *              is zero)
  *   max_unique capacity of coal_grad in rows (>= *num_unique), normally
  *              min(num_pairs, total_rows)
  *   coal_grad  [max_unique x dim] fp32; rows >= *num_unique are not written
  *   workspace, workspace_bytes
  *              optional (NULL, 0: none), sized with
  *              tc_backward_workspace_bytes for the step's pairs. With it,
- *              long segments are scheduled over persistent workgroups, and a
+ *              long segments are summed by workgroups of their own, and a
  *              segment [b, b + len) with len >= TC_BACKWARD_SPLIT_PAIRS that
  *              the workspace covers (b + len <= the num_pairs it was sized
  *              for) is summed in pieces instead of one chain: n =
