@@ -68,10 +68,7 @@ def test_tiles_up_to_the_last_pair(tmp_path):
              hk.block(src, "struct alignas(16) TileRec {"), hk.block(src, "struct SegLayout {")]
     for head in ("__device__ __forceinline__ int32_t tiles_of(", "__device__ TileRec tile_record(",
                  "__device__ __forceinline__ TileRec tile_of("):
-        if head in src:
-            parts.append(hk.block(src, head))
-    if "int32_t tiles_of(" not in src:
-        parts.append("static int32_t tiles_of(int32_t n) { return (n + kSortTile - 1) / kSortTile; }\n")
+        parts.append(hk.block(src, head))
     hk.run(hk.program(tmp_path, parts, TILES))
 
 
