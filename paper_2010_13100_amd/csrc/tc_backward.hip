@@ -633,20 +633,23 @@ __global__ __launch_bounds__(kListThreads) void k_backward_list(
 // The chain over ids sid[0..len) for one wavefront with 64-bit addresses, for
 // segments whose rows no buffer window holds: kFarRows rows are on their way at
 // once. Measured (us of the call; segments spread over 2.4 GB): 4000 of 48 to 79
-// rows of 1024 floats 756 row after row, 209 with 32 at a time (184 if the lane
-// groups of the short segments had them); of 80 to 200 1650 and 411; of 600 to
-// 900 11800 and 2260.
+// rows of 1024 floats 756 row after row, 214 with 32 at a time (184 if the lane
+// groups of the short segments had them); of 80 to 200 1650 and 420; of 600 to
+// 900 11800 and 2090. Ids are loaded by lane: loads of each by itself take a
+// register more, which the widest rows spill.
 constexpr int kFarRows = 32;
 __device__ __forceinline__ float far_chain(const float *__restrict__ grad, int32_t dim,
                                            const int32_t *__restrict__ sid, int32_t len,
                                            int32_t col) {
     const float *colp = grad + min(col, dim - 1);
+    const uint32_t lane = threadIdx.x & (kWave - 1);
     float acc = 0.f;
     for (uint32_t k = 0; k < uint32_t(len); k += kFarRows) {
         float row[kFarRows];
+        const int32_t id = sid[min(k + lane, uint32_t(len) - 1)];
 #pragma unroll
         for (uint32_t i = 0; i < kFarRows; ++i)
-            row[i] = colp[int64_t(sid[min(k + i, uint32_t(len) - 1)]) * dim];
+            row[i] = colp[int64_t(__builtin_amdgcn_readlane(id, i)) * dim];
 #pragma unroll
         for (uint32_t i = 0; i < kFarRows; ++i) acc = k + i < uint32_t(len) ? acc + row[i] : acc;
     }
