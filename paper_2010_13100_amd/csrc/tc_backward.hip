@@ -974,15 +974,18 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 // others the short segments. Chains of neighbouring segments (of one table,
 // sharing its rows of grad) are put on one XCD, workgroups going round-robin
 // over the XCDs, for the sake of its L2; any other mapping gives the same
-// results. Up to 512 columns all workgroups are resident at once, unless chains
-// take more than half of those places or the sweep is cut (below): more would sweep the short segments in
-// uneven windows (32 tables of 1M x 256: 2.42 ms with half as many workgroups
-// again, 2.14 ms with these; a million segments of 1 or 2 pairs, 320 columns 601
-// us with 8 workgroups per CU, 5 of them resident, and 550 with 5, 512 columns
-// 753 and 685). Chains are better off with the 8 (20 thousand segments of 1 to 90
-// pairs, 260 columns: 146 us, and 160 with 5), and wider rows, whose windows are
-// few, too (50 thousand segments of 1 to 20 pairs, 1024 columns: 274 us, and 282
-// with the 3 that are resident; 576 columns 123 and 127).
+// results. Up to 256 columns all workgroups are resident at once: more would
+// sweep the short segments in uneven windows (32 tables of 1M x 256: 2.42 ms with
+// half as many workgroups again, 2.14 ms with these). Of rows of 260 to 512
+// columns 5 of 8 workgroups per CU are resident; the sweep takes no more where
+// there are no chains (a million segments of 1 or 2 pairs, 320 columns 550 us and
+// 601 with all, 512 columns 685 and 753), or few beside a sweep of kEvenWindows
+// windows or more (a million segments of 1 to 3 pairs, 500 of them hot, 260 columns
+// 568 and 622), but all where workgroups come free as chains end (100 thousand
+// pairs of 30 tables of 2400 x 300, Zipf 1.2: 43.3 and 38.0 us). Chains are better
+// off with all 8 (20 thousand segments of 1 to 90 pairs, 260 columns: 146 us, and
+// 160 with 5), and wider rows, whose windows are few, too (50 thousand segments of
+// 1 to 20 pairs, 1024 columns: 274 us, and 282 with the 3 that are resident).
 // The chains' share of the workgroups is that of their pairs among all work,
 // with kSegmentCost pairs for each segment and kChainCost for each chain (8 x
 // 300k x 128, where many chains are short: 49.7 us without), so that both
@@ -1013,6 +1016,8 @@ __global__ __launch_bounds__(kBlock) void k_backward_short(
 // thousand segments in room for 5.2 million: 8.7 and 12.7 us).
 constexpr int kTurns = 8;
 constexpr int kTurnWindows = 32;
+// Windows from which a sweep beside few chains keeps to the resident workgroups.
+constexpr int kEvenWindows = 64;
 // Workgroups on a CU (wavefronts on a SIMD) by float4 chunks per lane.
 constexpr int rows_per_cu(int chunks) { return chunks == 1 ? 8 : 7 - chunks; }
 // Whether the sweep of `num` segments by `blocks` workgroups is cut into parts.
@@ -1063,10 +1068,11 @@ __global__ __launch_bounds__(kBlock, rows_per_cu(CHUNKS)) void k_backward_rows(
     const int32_t chain_blocks = chain_rounds * kXcds;
     if (int32_t(blockIdx.x) >= chain_blocks) {
         int32_t short_blocks = blocks - chain_blocks;
-        if (CHUNKS == 2 && !parts) {  // the resident ones, unless chains have most places
+        if (CHUNKS == 2 && !parts) {
             const int32_t resident = cus * rows_per_cu(CHUNKS);
-            short_blocks = min(short_blocks, chain_blocks <= resident / 2 ? resident - chain_blocks
-                                                                          : resident);
+            if (chain_blocks == 0 ||
+                (chain_blocks <= resident / 2 && num >= int64_t(kEvenWindows) * blocks * kWaves))
+                short_blocks = min(short_blocks, resident - chain_blocks);
             if (int32_t(blockIdx.x) >= chain_blocks + short_blocks) return;
         }
         const int32_t nwave = short_blocks * kWaves;
